@@ -15,8 +15,11 @@ BUILD = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("AM_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["am_api.cpp", "am_server.cpp", "am_setup.hip", "am_fused.hip", "am_residuals.hip", "am_plain.hip",
-           "am_static.hip"]
+# (source, defines): the fused kernel is one object per element type and basis
+# size, the slowest ones first
+SOURCES = [("am_fused.hip", (f"-DAM_FUSED_T={t}", f"-DAM_FUSED_NV={nv}")) for nv in (11, 8) for t in ("double", "float")]
+SOURCES += [(s, ()) for s in ("am_plain.hip", "am_setup.hip", "am_residuals.hip", "am_api.cpp", "am_server.cpp",
+                              "am_dispatch.cpp", "am_static.hip")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}",
           "-Wall", "-Wno-unused-function"]
@@ -25,9 +28,10 @@ DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-p
           ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(part) -> str:
+    src, defines = part
+    obj = os.path.join(BUILD, "_".join([os.path.splitext(src)[0], *(d.split("=")[1] for d in defines)]) + ".o")
+    cmd = [HIPCC, *COMMON, *defines, "-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".hip"):
         cmd[1:1] = ["-x", "hip"] + DEVICE
     else:

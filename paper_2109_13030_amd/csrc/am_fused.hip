@@ -179,8 +179,15 @@ __device__ __forceinline__ T row_dot(const T *op, int I, const T *v) {
   return acc0 + acc1;
 }
 
+// The body and its lambdas are inlined by force: left to itself the compiler
+// keeps the large ones (8 circles, FP64) as functions, and everything they
+// capture (the circles' sums, the basis rows, the state) then lives in
+// scratch memory, 0.6 to 1.8 KB a lane.  Inlined, FP64 with 3 circles (16
+// trajectories, 50 iterations) takes 204 us against 611, FP64 with 5 circles
+// (501 trajectories, 20 iterations, q = 127) 133 us against 558, FP32 with 8
+// circles (333 trajectories, 40 obstacles, 20 iterations) 173 us against 183.
 template <typename T, int NV, int C, int RED>
-__device__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds, const FusedLds &L,
+__device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds, const FusedLds &L,
                            int lane, int wave) {
   constexpr int A2 = pad4(2 * NV), N2 = 2 * NV;
   constexpr int NP = pad4(NV);   // basis rows padded to whole 4-row groups
@@ -381,7 +388,7 @@ __device__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds,
   // dz copies), then every channel advanced by the product of the update dz
   // (its blocks QS apart in LDS, read in this lane's slot order), the
   // positions in FP64
-  auto eval_xy = [&](bool step) {
+  auto eval_xy = [&](bool step) __attribute__((always_inline)) {
     T a0 = 0, b0 = 0, a1 = 0, a2 = 0, a3 = 0, b1 = 0, b2 = 0, b3 = 0;
 #pragma unroll
     for (int c = 0; c < NP / 4; ++c) {
@@ -408,7 +415,7 @@ __device__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds,
   // FP64 and rounded once
   auto off_x = [&](T ox) { return T(xa - double(ox)); };
   auto off_y = [&](T oy) { return T(ya - double(oy)); };
-  auto eval_psi = [&]() {
+  auto eval_psi = [&]() __attribute__((always_inline)) {
     T p = 0;
 #pragma unroll
     for (int c = 0; c < NP / 4; ++c) {
@@ -442,7 +449,7 @@ __device__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds,
   // obstacle, whose terms start the sums.
   T Sx[C], Sy[C];
   T xh = T(0), yh = T(0), rxl[C], ryl[C];
-  auto project_obstacle = [&](auto count, auto first, const Pair<T> o, const Quad<T> p) {
+  auto project_obstacle = [&](auto count, auto first, const Pair<T> o, const Quad<T> p) __attribute__((always_inline)) {
     constexpr int MC = decltype(count)::value;
     constexpr bool FIRST = decltype(first)::value;
     const T dxj = xh - o.x, dyj = yh - o.y;
@@ -467,7 +474,7 @@ __device__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds,
   };
   // The near obstacles of the (non-empty) mask, each one's LDS data loaded
   // while the previous one is projected (two register sets in turn).
-  auto project_near = [&](auto count, uint64_t mask) {
+  auto project_near = [&](auto count, uint64_t mask) __attribute__((always_inline)) {
     int j = __builtin_ctzll(mask);
     mask &= mask - 1;
     Pair<T> o0 = oxy[j * q + tt], o1;
@@ -508,7 +515,7 @@ __device__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds,
   T xvote = T(0), yvote = T(0), extvote = T(0);
   uint64_t near_set = 0;
   bool voted = false;
-  auto project_reduce = [&](bool with_psi) {
+  auto project_reduce = [&](bool with_psi) __attribute__((always_inline)) {
     const T ux = slack ? cc : cps, uy = slack ? ss : sps;
     const T x = T(xa), y = T(ya);   // for the vote and the projection
     if (!literal_alpha) {
@@ -1109,40 +1116,34 @@ hipError_t launch_tile(const Desc &single, const Desc *table, int nprob, int nbl
   }
 }
 
-// FP32: the small circle capacity when every problem of the launch fits it.
-template <int NV, int WAVES>
-hipError_t launch_f32(const Desc &single, const Desc *table, int nprob, int nblocks, hipStream_t st,
+// The small circle capacity when every problem of the launch fits it.
+template <typename T, int NV, int WAVES>
+hipError_t launch_c(const Desc &single, const Desc *table, int nprob, int nblocks, hipStream_t st,
                       size_t lds_bytes, int tile, int max_m) {
   if (max_m <= kSmallC)
-    return launch_tile<float, NV, kSmallC, WAVES>(single, table, nprob, nblocks, st, lds_bytes, tile);
-  return launch_tile<float, NV, AM_MAX_CIRCLES, WAVES>(single, table, nprob, nblocks, st, lds_bytes, tile);
+    return launch_tile<T, NV, kSmallC, WAVES>(single, table, nprob, nblocks, st, lds_bytes, tile);
+  return launch_tile<T, NV, AM_MAX_CIRCLES, WAVES>(single, table, nprob, nblocks, st, lds_bytes, tile);
 }
 
 }  // namespace
 
-size_t fused_lds_bytes(int q, int n, int nv, bool f64, int tile, int waves) {
-  return size_t(fused_layout(q, n, nv, tile, red_rows_for(waves), f64 ? 1 : 2).total) * (f64 ? 8 : 4);
-}
-
-// FP64 kernels take the default budget only, built without a wavefront
-// target (their registers do not fit 256 without spilling).
-hipError_t launch_fused(const Desc &single, const Desc *table, int nprob, int nblocks, bool f64,
-                        int nv, int max_m, hipStream_t st, size_t lds_bytes, int tile, int waves) {
-  if (nblocks <= 0) return hipSuccess;
-  if (max_m < 1 || max_m > AM_MAX_CIRCLES) return hipErrorInvalidValue;
-  constexpr int MC = AM_MAX_CIRCLES;
-  if (f64) {
-    if (waves != 2) return hipErrorInvalidValue;
-    if (nv == 11) return launch_tile<double, 11, MC, 1>(single, table, nprob, nblocks, st, lds_bytes, tile);
-    if (nv == 8) return launch_tile<double, 8, MC, 1>(single, table, nprob, nblocks, st, lds_bytes, tile);
-  } else if (waves == 2) {
-    if (nv == 11) return launch_f32<11, 2>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
-    if (nv == 8) return launch_f32<8, 2>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
-  } else if (waves == 3) {
-    if (nv == 11) return launch_f32<11, 3>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
-    if (nv == 8) return launch_f32<8, 3>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
+// This file is compiled once per element type and basis size (AM_FUSED_T,
+// AM_FUSED_NV: four objects, built in parallel; every kernel is inlined
+// whole, so one object with all of them takes minutes).
+template <typename T, int NV>
+hipError_t launch_fused_part(const Desc &single, const Desc *table, int nprob, int nblocks, int max_m, hipStream_t st,
+                             size_t lds_bytes, int tile, int waves) {
+  // FP64 kernels take the default budget only, built without a wavefront
+  // target (their registers do not fit 256 without spilling)
+  if constexpr (sizeof(T) == 8) {
+    if (waves == 2) return launch_c<T, NV, 1>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
+  } else {
+    if (waves == 2) return launch_c<T, NV, 2>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
+    if (waves == 3) return launch_c<T, NV, 3>(single, table, nprob, nblocks, st, lds_bytes, tile, max_m);
   }
   return hipErrorInvalidValue;
 }
+template hipError_t launch_fused_part<AM_FUSED_T, AM_FUSED_NV>(const Desc &, const Desc *, int, int, int, hipStream_t,
+                                                               size_t, int, int);
 
 }  // namespace amk

@@ -238,6 +238,16 @@ def test_f32_circle_counts_against_oracle(m):
     _fp32_gate(pb, init, 30)
 
 
+@pytest.mark.parametrize("m", [2, 4, 5, 6, 8])
+def test_f64_circle_counts_against_oracle(m):
+    """FP64 through both circle capacities of the kernel (5 and 8)."""
+    import dataclasses
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], circles=m)
+    pb = inputs.make_problem(cfg, 21)
+    init = inputs.make_initial(pb, 5, 22, cfg.sigma)
+    _compare_f64(pb, init, 12)
+
+
 def _largest_problem(B):
     import dataclasses
     cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=128, n_obs=64, circles=8)
