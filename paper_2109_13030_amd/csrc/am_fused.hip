@@ -22,8 +22,7 @@
 //    from the current point is accumulated, so residuals are formed without
 //    cancellation.  That deviation is zero for circle centres outside the
 //    ellipse, so obstacles farther from the robot centre than the farthest
-//    circle plus the larger semi-axis are skipped (a wave-wide vote per
-//    obstacle).
+//    circle plus the larger semi-axis are skipped (a list per lane).
 //  * lambda <- lambda - rho F^T (F xi - g) (eq. update_lambda_1) and the
 //    next xi1 right-hand side lambda + rho F^T g share the single reduction
 //    F^T (F xi - g).
@@ -72,7 +71,11 @@ namespace {
 // here; fewer registers and no dead circle slots) or AM_MAX_CIRCLES.
 constexpr int kSmallC = 5;
 constexpr int kVoteChunk = 8;   // obstacles whose positions are loaded together in the vote
-constexpr double kVoteMargin = 0.25;   // [m] slack of the near-obstacle set, see project_reduce
+// [m] slack of the near-obstacle lists, see project_reduce: a wider one renews
+// them less often but holds more obstacles (an iteration at B = 4096, n = 20
+// with 0.12 / 0.25 / 0.4 / 0.6 m: 14.6 / 13.2 / 12.7 / 12.5 us; B = 1000, n =
+// 10: 2.42 / 2.30 / 2.26 / 2.30 us)
+constexpr double kVoteMargin = 0.45;
 
 // Wave-uniform copies of descriptor fields: the compiler then keeps them in
 // scalar registers and treats loops over them as uniform.
@@ -86,6 +89,8 @@ __device__ __forceinline__ double uni(double v) {
   const int hi = __builtin_amdgcn_readfirstlane(int(b >> 32));
   return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | (static_cast<unsigned int>(lo)));
 }
+
+__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 // Value of the neighbouring lane (lane ^ 1) through a DPP quad permutation.
 __device__ __forceinline__ float lane_xor1(float v) {
@@ -472,35 +477,60 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
       }
     }
   };
-  // The near obstacles of the (non-empty) mask, each one's LDS data loaded
-  // while the previous one is projected (two register sets in turn).
-  auto project_near = [&](auto count, uint64_t mask) __attribute__((always_inline)) {
-    int j = __builtin_ctzll(mask);
+  // This lane's near obstacles, lowest index first, each one's LDS data
+  // loaded while the previous one is projected (two register sets in turn).
+  // Every lane walks its own list, so a pass over the wave takes as many
+  // steps as the fullest lane has near obstacles (about 2.4 with 20 moving
+  // obstacles), not as many as are near some lane (4.7): an obstacle is near
+  // for a few seconds of the horizon only (B = 4096, n = 20, K = 20: 396 ->
+  // 354 us; B = 1000, n = 10: 84 -> 79 us).  A lane whose list is done reads
+  // the last obstacle with ab = 0, which adds exactly zero (fmax drops the NaN
+  // of 0 * inf).  One word of the list holds obstacles 0..31; those past 31
+  // follow in a plain loop.
+  const int qstep = q * int(sizeof(Pair<T>));
+  const char *oxy_t = reinterpret_cast<const char *>(oxy + tt);
+  auto next_near = [&](uint32_t &mask, int base, Pair<T> &o, Quad<T> &p) __attribute__((always_inline)) {
+    uint32_t low;   // lowest set bit, all ones when there is none
+    asm("v_ffbl_b32 %0, %1" : "=v"(low) : "v"(mask));
+    const uint32_t j = base + umin(low, uint32_t(n - 1 - base));
     mask &= mask - 1;
-    Pair<T> o0 = oxy[j * q + tt], o1;
-    Quad<T> p0 = opq[j * 2], p1;
-    bool more = mask != 0;
-    j = more ? __builtin_ctzll(mask) : j;
-    mask &= mask - 1;
-    o1 = oxy[j * q + tt];
-    p1 = opq[j * 2];
-    project_obstacle(count, std::true_type(), o0, p0);
-    if (!more) return;
-    while (true) {
-      more = mask != 0;
-      j = more ? __builtin_ctzll(mask) : j;
-      mask &= mask - 1;
-      o0 = oxy[j * q + tt];
-      p0 = opq[j * 2];
-      project_obstacle(count, std::false_type(), o1, p1);
-      if (!more) break;
-      more = mask != 0;
-      j = more ? __builtin_ctzll(mask) : j;
-      mask &= mask - 1;
-      o1 = oxy[j * q + tt];
-      p1 = opq[j * 2];
+    o = *reinterpret_cast<const Pair<T> *>(oxy_t + __umul24(j, uint32_t(qstep)));
+    p = opq[j * 2];
+    p.c = int(low) < 0 ? T(0) : p.c;
+  };
+  // keeps the loads of a next obstacle before this point (the compiler would
+  // sink them to their first use and wait there)
+  auto pin = [](Pair<T> &o, Quad<T> &p) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(o.x), "+v"(o.y), "+v"(p.a), "+v"(p.b), "+v"(p.c));
+  };
+  auto project_near = [&](auto count, uint32_t lo, uint32_t hi) __attribute__((always_inline)) {
+    Pair<T> o0, o1;
+    Quad<T> p0, p1;
+    if (__ballot(lo != 0) != 0) {
+      next_near(lo, 0, o0, p0);
+      bool more = __ballot(lo != 0) != 0;
+      next_near(lo, 0, o1, p1);
+      project_obstacle(count, std::true_type(), o0, p0);
+      pin(o1, p1);
+      while (more) {
+        more = __ballot(lo != 0) != 0;
+        next_near(lo, 0, o0, p0);
+        project_obstacle(count, std::false_type(), o1, p1);
+        pin(o0, p0);
+        if (!more) break;
+        more = __ballot(lo != 0) != 0;
+        next_near(lo, 0, o1, p1);
+        project_obstacle(count, std::false_type(), o0, p0);
+        pin(o1, p1);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < C; ++i) { Sx[i] = T(0); Sy[i] = T(0); }
+    }
+    if (n <= 32) return;
+    while (__ballot(hi != 0) != 0) {
+      next_near(hi, 32, o0, p0);
       project_obstacle(count, std::false_type(), o0, p0);
-      if (!more) break;
     }
   };
 
@@ -511,34 +541,38 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   // `rp` keeps this lane's heading residual psi_sign (psi - psi_hat) for
   // the next heading step.
   T tr = T(0), rp = T(0);
-  // near-obstacle set of the last vote and the positions it was taken at
-  T xvote = T(0), yvote = T(0), extvote = T(0);
-  uint64_t near_set = 0;
-  bool voted = false;
+  // near-obstacle lists of the last vote, and the positions and the bound of
+  // |u|^2 it was taken for
+  T xvote = T(0), yvote = T(0), u2lim = T(0);
+  uint32_t near_lo = 0, near_hi = 0;
+  bool near_any = false, voted = false;
   auto project_reduce = [&](bool with_psi) __attribute__((always_inline)) {
     const T ux = slack ? cc : cps, uy = slack ? ss : sps;
     const T x = T(xa), y = T(ya);   // for the vote and the projection
     if (!literal_alpha) {
-      // Wave-wide vote: obstacles within ext + max(a, b) + margin of some
-      // lane's robot centre, ext = max|r_i| |u| the reach of its circles.
-      // The set stays valid while every lane has moved by less than the
-      // margin minus any growth of ext since the vote (an obstacle outside
-      // it is then still farther than ext + max(a, b), where every circle
-      // is outside the ellipse and contributes exactly zero), so the vote
-      // is repeated only when some lane has moved that far.  The positions
-      // of a chunk of obstacles are loaded before any is tested.
-      // (|u| from the hardware square root, enlarged by 1e-6 so that the
-      // rounding of the estimate cannot make ext too small)
-      const T ext = rmax * Num<T>::sqrt_fast(ux * ux + uy * uy) * T(1.000001);
+      // Near obstacles of this lane: those within ext + max(a, b) + margin of
+      // its robot centre, ext = max|r_i| |u| the reach of its circles.  The
+      // lists stay valid while every lane has moved by at most the margin
+      // and |u|^2 is within the bound that ext was formed for (an obstacle
+      // outside a lane's list is then still farther than its reach +
+      // max(a, b), where every circle is outside the ellipse and contributes
+      // exactly zero), so they are renewed only when some lane breaks that.
+      // The positions of a chunk of obstacles are loaded before any is
+      // tested.  (|u| from the hardware square root, enlarged by 1e-6 so
+      // that the rounding of the estimate cannot make ext too small)
       const T margin = T(kVoteMargin);
-      const T dxv = x - xvote, dyv = y - yvote, room = margin - (ext - extvote);
-      const bool stale = tv & !(room > T(0) && dxv * dxv + dyv * dyv <= room * room);
+      const T u2 = ux * ux + uy * uy;
+      const T dxv = x - xvote, dyv = y - yvote;
+      const bool stale = tv & !(u2 <= u2lim && dxv * dxv + dyv * dyv <= T(0.998) * margin * margin);
       if (!voted || __ballot(stale) != 0) {
         voted = true;
         xvote = x;
         yvote = y;
-        extvote = ext;
-        near_set = 0;
+        // (headings keep |u| = 1; the slack copies move, so they get room)
+        u2lim = slack ? T(1.1) * u2 : fmax(T(1.001), u2);
+        const T ext = rmax * Num<T>::sqrt_fast(u2lim) * T(1.000001);
+        const T extm = ext + margin;
+        near_lo = near_hi = 0;
         for (int j0 = 0; j0 < n; j0 += kVoteChunk) {
           Pair<T> o[kVoteChunk];
           T am[kVoteChunk];
@@ -548,18 +582,22 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
             o[k] = oxy[(j0 + k) * q + tt];
             am[k] = op[(j0 + k) * 8 + OP_AMAX];
           }
+          uint32_t bits = 0;
 #pragma unroll
           for (int k = 0; k < kVoteChunk; ++k) {
             if (j0 + k >= n) break;   // padding of the last chunk
             const T dx = x - o[k].x, dy = y - o[k].y;
-            const T reach = ext + am[k] + margin;
-            const bool near = tv & (dx * dx + dy * dy < reach * reach);
-            if (__ballot(near) != 0) near_set |= uint64_t(1) << (j0 + k);
+            const T reach = extm + am[k];
+            bits |= dx * dx + dy * dy < reach * reach ? 1u << k : 0u;
           }
+          bits = tv ? bits << (j0 & 31) : 0u;
+          if (j0 < 32) near_lo |= bits;
+          else near_hi |= bits;
         }
+        near_any = __ballot((near_lo | near_hi) != 0) != 0;
       }
       // active obstacles
-      if (near_set) {
+      if (near_any) {
         xh = x;
         yh = y;
         const T xl = T(xa - double(xh)), yl = T(ya - double(yh));
@@ -570,10 +608,12 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
         }
         // exact circle counts for m = C, C - 1 and C - 2 (robots of 3 to 5
         // circles with C = 5), the tested form otherwise
-        if (m == C) project_near(std::integral_constant<int, C>(), near_set);
-        else if (C > 1 && m == C - 1) project_near(std::integral_constant<int, (C > 1 ? C - 1 : 0)>(), near_set);
-        else if (C > 2 && m == C - 2) project_near(std::integral_constant<int, (C > 2 ? C - 2 : 0)>(), near_set);
-        else project_near(std::integral_constant<int, 0>(), near_set);
+        if (m == C) project_near(std::integral_constant<int, C>(), near_lo, near_hi);
+        else if (C > 1 && m == C - 1)
+          project_near(std::integral_constant<int, (C > 1 ? C - 1 : 0)>(), near_lo, near_hi);
+        else if (C > 2 && m == C - 2)
+          project_near(std::integral_constant<int, (C > 2 ? C - 2 : 0)>(), near_lo, near_hi);
+        else project_near(std::integral_constant<int, 0>(), near_lo, near_hi);
       } else {
 #pragma unroll
         for (int i = 0; i < C; ++i) { Sx[i] = T(0); Sy[i] = T(0); }

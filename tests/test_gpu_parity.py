@@ -248,6 +248,19 @@ def test_f64_circle_counts_against_oracle(m):
     _compare_f64(pb, init, 12)
 
 
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64])
+def test_obstacle_counts_against_oracle(n):
+    """Obstacle counts around the two words of a lane's near-obstacle list,
+    among crowded static and moving scenes, FP64 and FP32."""
+    import dataclasses
+    for dynamic in (False, True):
+        cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=40, n_obs=n, dynamic=dynamic)
+        pb = inputs.make_problem(cfg, 51 + n)
+        init = inputs.make_initial(pb, 5, 52, cfg.sigma)
+        _compare_f64(pb, init, 12)
+        _fp32_gate(pb, init, 12)
+
+
 def _largest_problem(B):
     import dataclasses
     cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=128, n_obs=64, circles=8)
