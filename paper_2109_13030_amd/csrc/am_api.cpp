@@ -23,8 +23,7 @@ struct am_handle {
   bool f64;
   int tile = amk::kDefaultTile;   // trajectories per block of the fused kernel
   int waves = amk::kDefaultWaves; // register budget of the fused kernel (wavefronts per SIMD)
-  double *buf64;       // all FP64 constants
-  void *bufT;          // typed copies
+  void *buf = nullptr;  // all constants
   Consts c;
 };
 
@@ -85,8 +84,8 @@ Desc make_desc(const am_handle *h, const am_problem *p, int32_t batch, int32_t i
   Desc d;
   std::memset(&d, 0, sizeof d);
   const Consts &c = h->c;
-  d.U = c.tU; d.V = c.tV; d.W = c.tW; d.M1 = c.tM1; d.H1 = c.tH1; d.M2 = c.tM2; d.H2 = c.tH2;
-  d.GF = c.tGF; d.N = c.tN; d.Ut = c.tUt; d.R = c.R; d.Rinv = c.Rinv; d.Ud = c.U; d.Abc = c.Abc; d.H1d = c.H1;
+  d.U = c.tU; d.V = c.tV; d.W = c.tW; d.M1 = c.tM1; d.M2 = c.tM2; d.H2 = c.tH2;
+  d.N = c.tN; d.Ut = c.tUt; d.R = c.R; d.Rinv = c.Rinv; d.Ud = c.U; d.Abc = c.Abc; d.H1d = c.H1;
   d.Qd = c.G + 2 * size_t(h->shape.nv) * h->shape.nv;   // the third Gram matrix, W^T W
   d.ox = p->obs_x; d.oy = p->obs_y; d.oa = p->obs_a; d.ob = p->obs_b;
   d.cx = st->cx; d.cc = st->cc; d.cy = st->cy; d.cs = st->cs; d.cpsi = st->cpsi;
@@ -217,58 +216,33 @@ int am_setup(const am_shape *s, am_handle **out) {
   if (e != hipSuccess) { delete h; return hip_fail(e, "hipGetDevice"); }
 
   const int q = s->q, nv = s->nv, n2 = 2 * nv, N1 = n2 + 6, N2 = nv + 6;
-  // FP64 carve-up (in doubles)
-  size_t sizes[] = {size_t(q * nv), size_t(q * nv), size_t(q * nv),      // P Pd Pdd
-                    size_t(q * nv), size_t(q * nv), size_t(q * nv),      // U V W
-                    size_t(nv * nv), size_t(nv * nv), size_t(3 * nv * nv),
-                    size_t(N1 * N1), size_t(N2 * N2), size_t(2 * N1 * N1), size_t(2 * N2 * N2),
-                    size_t(n2 * n2), size_t(n2 * 6), size_t(nv * nv), size_t(nv * 6), size_t(n2 * n2),
-                    size_t(N1 * N1), size_t(N2 * N2), 8, size_t(AM_MAX_CIRCLES), size_t(q * nv),
-                    size_t(n2 * n2), size_t(6 * nv)};
-  const int nparts = int(sizeof(sizes) / sizeof(sizes[0]));
-  size_t off[32], tot = 0;
-  for (int i = 0; i < nparts; ++i) { off[i] = tot; tot += align_up(sizes[i], 32); }
-  e = hipMalloc(&h->buf64, tot * sizeof(double));
-  if (e != hipSuccess) { delete h; return fail(AM_ERR_NOMEM, "hipMalloc of %zu bytes failed", tot * 8); }
-  double *b = h->buf64;
+  // one allocation: the FP64 constants, then the typed ones
   Consts &c = h->c;
-  c.P = b + off[0]; c.Pd = b + off[1]; c.Pdd = b + off[2]; c.U = b + off[3]; c.V = b + off[4];
-  c.W = b + off[5]; c.R = b + off[6]; c.Rinv = b + off[7]; c.G = b + off[8]; c.K1 = b + off[9];
-  c.K2 = b + off[10]; c.A1 = b + off[11]; c.A2 = b + off[12]; c.M1 = b + off[13]; c.H1 = b + off[14];
-  c.M2 = b + off[15]; c.H2 = b + off[16]; c.GF = b + off[17]; c.K1b_inv = b + off[18];
-  c.K2b_inv = b + off[19]; c.status = b + off[20];
-  double *r_dev = b + off[21];
-  c.Ut = b + off[22];
-  c.N = b + off[23];
-  c.Abc = b + off[24];
-
-  // typed carve-up (in elements)
-  const size_t es = h->f64 ? 8 : 4;
-  size_t tsz[] = {size_t(q * nv), size_t(q * nv), size_t(q * nv), size_t(n2 * n2), size_t(n2 * 6),
-                  size_t(nv * nv), size_t(nv * 6), size_t(n2 * n2), size_t(q * nv), size_t(q * nv),
-                  size_t(q * nv), size_t(q * nv), size_t(n2 * n2)};
-  constexpr int ntyped = int(sizeof(tsz) / sizeof(tsz[0]));
-  size_t toff[16], ttot = 0;
-  for (int i = 0; i < ntyped; ++i) { toff[i] = ttot; ttot += align_up(tsz[i], 64); }
-  e = hipMalloc(&h->bufT, ttot * es);
-  if (e != hipSuccess) {
-    (void)hipFree(h->buf64);
-    delete h;
-    return fail(AM_ERR_NOMEM, "hipMalloc of %zu bytes failed", ttot * es);
-  }
-  char *tb = static_cast<char *>(h->bufT);
-  void **tp[] = {&c.tU, &c.tV, &c.tW, &c.tM1, &c.tH1, &c.tM2, &c.tH2, &c.tGF, &c.tP, &c.tPd, &c.tPdd, &c.tUt, &c.tN};
-  static_assert(sizeof(tp) / sizeof(tp[0]) == ntyped, "typed buffers");
-  for (int i = 0; i < ntyped; ++i) *tp[i] = tb + toff[i] * es;
+  const size_t qn = size_t(q * nv), es = h->f64 ? 8 : 4;
+  const struct { double **p; size_t count; } dparts[] = {
+      {&c.P, qn}, {&c.Pd, qn}, {&c.Pdd, qn}, {&c.U, qn}, {&c.V, qn}, {&c.W, qn},
+      {&c.R, size_t(nv * nv)}, {&c.Rinv, size_t(nv * nv)}, {&c.G, size_t(3 * nv * nv)},
+      {&c.K1, size_t(N1 * N1)}, {&c.K2, size_t(N2 * N2)}, {&c.M1, size_t(n2 * n2)}, {&c.H1, size_t(n2 * 6)},
+      {&c.M2, size_t(nv * nv)}, {&c.H2, size_t(nv * 6)}, {&c.Abc, size_t(6 * nv)},
+      {&c.K1b_inv, size_t(N1 * N1)}, {&c.K2b_inv, size_t(N2 * N2)}, {&c.status, 8}};
+  const struct { void **p; size_t count; } tparts[] = {
+      {&c.tU, qn}, {&c.tV, qn}, {&c.tW, qn}, {&c.tP, qn}, {&c.tPd, qn}, {&c.tPdd, qn}, {&c.tUt, qn},
+      {&c.tM1, size_t(n2 * n2)}, {&c.tM2, size_t(nv * nv)}, {&c.tH2, size_t(nv * 6)}, {&c.tN, size_t(n2 * n2)}};
+  size_t bytes = 0;
+  for (const auto &p : dparts) bytes += align_up(p.count * 8, 256);
+  for (const auto &p : tparts) bytes += align_up(p.count * es, 256);
+  e = hipMalloc(&h->buf, bytes);
+  if (e != hipSuccess) { delete h; return fail(AM_ERR_NOMEM, "hipMalloc of %zu bytes failed", bytes); }
+  char *at = static_cast<char *>(h->buf);
+  for (const auto &p : dparts) { *p.p = reinterpret_cast<double *>(at); at += align_up(p.count * 8, 256); }
+  for (const auto &p : tparts) { *p.p = at; at += align_up(p.count * es, 256); }
 
   hipStream_t stream = nullptr;
   double status = -1.0;
   int rc = AM_OK;
   if ((e = hipStreamCreateWithFlags(&stream, hipStreamNonBlocking)) != hipSuccess) {
     rc = hip_fail(e, "hipStreamCreateWithFlags");
-  } else if ((e = hipMemcpyAsync(r_dev, h->r, sizeof(double) * s->m, hipMemcpyHostToDevice, stream)) != hipSuccess) {
-    rc = hip_fail(e, "hipMemcpyAsync");
-  } else if ((e = amk::launch_setup(h->shape, r_dev, c, h->f64, stream)) != hipSuccess) {
+  } else if ((e = amk::launch_setup(h->shape, h->r, c, h->f64, stream)) != hipSuccess) {
     rc = hip_fail(e, "setup kernel launch");
   } else if ((e = hipMemcpyAsync(&status, c.status, sizeof(double), hipMemcpyDeviceToHost, stream)) != hipSuccess) {
     rc = hip_fail(e, "hipMemcpyAsync");
@@ -296,8 +270,7 @@ int am_setup(const am_shape *s, am_handle **out) {
 
 void am_destroy(am_handle *h) {
   if (!h) return;
-  if (h->buf64) (void)hipFree(h->buf64);
-  if (h->bufT) (void)hipFree(h->bufT);
+  if (h->buf) (void)hipFree(h->buf);
   delete h;
 }
 

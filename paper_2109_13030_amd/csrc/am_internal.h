@@ -24,9 +24,8 @@ constexpr int kDefaultWaves = 2;
 struct Desc {
   // constants built by the setup kernel (orthonormal basis, KKT inverses)
   const void *U, *V, *W;     // [q][nv]: x = U z, xdot = V z, xddot = W z
-  const void *M1, *H1;       // xi1: [2nv][2nv] and [2nv][6]
+  const void *M1;            // xi1: [2nv][2nv]
   const void *M2, *H2;       // xi2: [nv][nv] and [nv][6]
-  const void *GF;            // [2nv][2nv] F^T F of one axis in the z basis
   const void *N;             // [2nv][2nv] M1 Q (Q: smoothness cost of one axis in the z basis)
   const void *Ut;            // [q][nv] U M2^T (heading rows premultiplied by M2)
   const double *R, *Rinv;    // z = R c (Bernstein c), [nv][nv]
@@ -55,22 +54,20 @@ struct Consts {
   double *P, *Pd, *Pdd;          // [q][nv] Bernstein basis and derivatives
   double *U, *V, *W;             // [q][nv]
   double *R, *Rinv;              // [nv][nv]
-  double *G;                     // scratch: 3 Gram matrices [3][nv][nv]
-  double *K1, *K2;               // z-space KKT [N1][N1], [N2][N2]
-  double *A1, *A2;               // Gauss-Jordan work [N][2N]
-  double *M1, *H1, *M2, *H2, *GF;
-  double *N;                     // [2nv][2nv] M1 Q
+  double *G;                     // 3 Gram matrices [3][nv][nv]
+  double *K1, *K2;               // inverses of the z-space KKT matrices [N1][N1], [N2][N2]
+  double *M1, *H1, *M2, *H2;
   double *Abc;                   // [6][nv] boundary rows in the z basis
   double *K1b_inv, *K2b_inv;     // Bernstein-space inverses (diagnostics)
-  double *Ut;                    // [q][nv] U M2^T
   double *status;                // [0]: 0 ok, 1 singular xi1 KKT, 2 singular xi2 KKT
-  void *tU, *tV, *tW, *tM1, *tH1, *tM2, *tH2, *tGF;  // typed copies
-  void *tP, *tPd, *tPdd, *tUt, *tN;
+  void *tU, *tV, *tW, *tM1, *tM2, *tH2;   // typed copies
+  void *tP, *tPd, *tPdd;
+  void *tUt, *tN;                // U M2^T and M1 Q, typed
 };
 
 // Launchers (defined in the .hip files).
-hipError_t launch_setup(const am_shape &s, const double *r_dev, const Consts &c, bool f64,
-                        hipStream_t st);
+// r: the circle offsets (host)
+hipError_t launch_setup(const am_shape &s, const double *r, const Consts &c, bool f64, hipStream_t st);
 size_t fused_lds_bytes(int q, int n, int nv, bool f64, int tile, int waves);
 // max_m: the largest circle count of the launch's problems (picks the
 // kernel's circle capacity)

@@ -1,6 +1,6 @@
 // am_setup.hip -- one-time FP64 construction of the constant operators of the
 // batched AM iteration (Sec. III-A eqs. over_2/over_3; Sec. IV: F^T F is
-// formed once), on the GPU in a single workgroup.
+// formed once), on the GPU.
 //
 // The Bernstein basis P (eq. param) is factored P = U R with U orthonormal on
 // the time grid.  The iteration runs on z = R c: x = U z, xdot = V z,
@@ -9,341 +9,424 @@
 // well conditioned and its FP32 application does not amplify rounding the way
 // the Bernstein-coordinate inverse does.  The KKT matrices are assembled in z
 // coordinates and inverted by Gauss-Jordan elimination with partial pivoting.
+//
+// A set-up is a chain of small dependent steps, so latency bounds it: the
+// first kernel is one workgroup that holds every matrix in LDS (about 100 KB)
+// and runs each step on as many lanes as it has entries, the second spreads
+// what only depends on its results (products for the iteration, Bernstein
+// inverses, typed copies) over the GPU.  A first form in one workgroup with
+// its matrices in global memory (serial pivot searches, one block-wide
+// reduction per Gram-Schmidt coefficient) took 556 us; these take 59 + 13 us
+// (q = 100, nv = 11: basis 8, QR 17, elimination 25, Gram matrices 2 us).
 #include <hip/hip_runtime.h>
 
+#include "am_device.h"
 #include "am_internal.h"
 
 namespace amk {
 namespace {
 
-constexpr int kSetupThreads = 256;
+constexpr int kSetupThreads = 1024;
+constexpr int kPackBlocks = 6, kPackThreads = 256;
 
-__device__ double bernstein(int deg, int i, double tau) {
+struct SetupArgs {
+  int q, m, n, flags, f64;
+  double tf, rho;
+  double r[AM_MAX_CIRCLES];
+  Consts c;
+};
+
+// LDS of the first kernel, in doubles.
+template <int NV>
+struct SetupLds {
+  static constexpr int N1 = 2 * NV + 6, N2 = NV + 6;
+  int P, Pd, Pdd, U, V, W, R, Rinv, G, bin, vcol, dj, A1, A2, total;
+  __host__ __device__ explicit SetupLds(int q) {
+    int o = 0;
+    P = o; o += q * NV;
+    Pd = o; o += q * NV;
+    Pdd = o; o += q * NV;
+    U = o; o += q * NV;
+    V = o; o += q * NV;
+    W = o; o += q * NV;
+    R = o; o += NV * NV;
+    Rinv = o; o += NV * NV;
+    G = o; o += 3 * NV * NV;
+    bin = o; o += 3 * NV;
+    vcol = o; o += 2 * AM_MAX_Q;
+    dj = o; o += NV;
+    A1 = o; o += 2 * N1 * (2 * N1 + 1);   // augmented [N][2N + 1], two buffers
+    A2 = o; o += 2 * N2 * (2 * N2 + 1);
+    total = o;
+  }
+};
+
+// Bernstein polynomial B_{deg,i}(tau) with the binomials of `deg` in `bin`;
+// zero outside 0 <= i <= deg.
+__device__ __noinline__ double bernstein(const double *bin, int deg, int i, double tau) {
   if (i < 0 || i > deg) return 0.0;
-  // C(deg, i) tau^i (1 - tau)^(deg - i), binomial built multiplicatively
-  double c = 1.0;
-  for (int k = 1; k <= i; ++k) c = c * double(deg - i + k) / double(k);
-  double v = c;
+  double v = bin[i];
   for (int k = 0; k < i; ++k) v *= tau;
   for (int k = 0; k < deg - i; ++k) v *= (1.0 - tau);
   return v;
 }
 
-// Block-wide sum of one value per thread.
-__device__ double block_sum(double v, double *sh) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int s = kSetupThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) sh[tid] += sh[tid + s];
-    __syncthreads();
-  }
-  double r = sh[0];
-  __syncthreads();
-  return r;
+__device__ __forceinline__ double lane_sum(double v) {
+  return wave_all(v, 0.0, [](double a, double b) { return a + b; });
 }
 
-// In-place Gauss-Jordan inverse of the N x N matrix stored in the left half
-// of aug [N][2N] (right half is set to I here).  Returns false if a pivot is
-// below tol * max|K|.
-__device__ bool gauss_jordan(double *aug, int N, double *sh, int *ish) {
-  const int tid = threadIdx.x, W2 = 2 * N;
-  for (int idx = tid; idx < N * N; idx += kSetupThreads) {
-    int r = idx / N, c = idx % N;
-    aug[r * W2 + N + c] = (r == c) ? 1.0 : 0.0;
-  }
-  double big = 0.0;
-  for (int idx = tid; idx < N * N; idx += kSetupThreads)
-    big = fmax(big, fabs(aug[(idx / N) * W2 + idx % N]));
-  sh[tid] = big;
-  __syncthreads();
-  for (int s = kSetupThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) sh[tid] = fmax(sh[tid], sh[tid + s]);
-    __syncthreads();
-  }
-  const double tol = 1e-13 * sh[0];
-  __syncthreads();
-  bool ok = sh[0] > 0.0;
-  for (int col = 0; col < N && ok; ++col) {
-    if (tid == 0) {
-      int p = col;
-      for (int r = col + 1; r < N; ++r)
-        if (fabs(aug[r * W2 + col]) > fabs(aug[p * W2 + col])) p = r;
-      ish[0] = p;
-      ish[1] = fabs(aug[p * W2 + col]) > tol;
+// One column step of the Gauss-Jordan elimination of the augmented [N][2N]
+// matrix (row stride 2N + 1: a column's entries lie in different LDS banks):
+// reads `a`, writes `b`.  Every wavefront finds the pivot row by itself (the
+// first row of largest magnitude at or below `col`), so a step needs one
+// barrier.  Returns false if the pivot is at most `tol`.
+template <int N, int THREADS>
+__device__ bool gj_step(const double *__restrict__ a, double *__restrict__ b, int col, double tol, int tid) {
+  constexpr int W2 = 2 * N, S = W2 + 1, E = (N * W2 + THREADS - 1) / THREADS;
+  static_assert(N <= kWave, "one lane per row");
+  const int lane = threadIdx.x & (kWave - 1);
+  const bool row = lane >= col && lane < N;
+  const double mine = row ? fabs(a[lane * S + col]) : -1.0;
+  const double top = wave_all(mine, -1.0, [](double x, double y) { return fmax(x, y); });
+  const unsigned long long at = __ballot(row && mine == top);
+  if (!(top > tol) || at == 0) return false;   // (a NaN matrix has no pivot)
+  const int p = __builtin_ctzll(at);
+  double old[E], fac[E], prow[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int idx = tid + k * THREADS, r = idx / W2, c = idx % W2;
+    if (idx < N * W2) {
+      const int src = r == p ? col : r;   // rows p and col change places
+      old[k] = a[src * S + c];
+      fac[k] = a[src * S + col];
+      prow[k] = a[p * S + c];
     }
-    __syncthreads();
-    const int p = ish[0];
-    ok = ish[1] != 0;
-    if (!ok) break;
-    if (p != col)
-      for (int c = tid; c < W2; c += kSetupThreads) {
-        double t = aug[col * W2 + c];
-        aug[col * W2 + c] = aug[p * W2 + c];
-        aug[p * W2 + c] = t;
-      }
-    __syncthreads();
-    const double inv = 1.0 / aug[col * W2 + col];
-    __syncthreads();
-    for (int c = tid; c < W2; c += kSetupThreads) aug[col * W2 + c] *= inv;
-    // elimination factors of column `col`, read before any row is updated
-    double *fac = sh;
-    for (int r = tid; r < N; r += kSetupThreads) fac[r] = (r == col) ? 0.0 : aug[r * W2 + col];
-    __syncthreads();
-    for (int idx = tid; idx < N * W2; idx += kSetupThreads) {
-      const int r = idx / W2, c = idx % W2;
-      if (r != col) aug[r * W2 + c] -= fac[r] * aug[col * W2 + c];
-    }
-    __syncthreads();
   }
-  return ok;
+  const double inv = 1.0 / a[p * S + col];
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int idx = tid + k * THREADS, r = idx / W2, c = idx % W2;
+    if (idx < N * W2) {
+      const double pr = prow[k] * inv;
+      b[r * S + c] = r == col ? pr : old[k] - fac[k] * pr;
+    }
+  }
+  return true;
 }
 
-template <typename T>
-__device__ void to_typed(const double *src, void *dst, int count) {
-  T *d = static_cast<T *>(dst);
-  for (int i = threadIdx.x; i < count; i += kSetupThreads) d[i] = T(src[i]);
-}
-
-struct SetupArgs {
-  int q, nv, m, n, flags, f64;
-  double tf, rho;
-  const double *r;
-  Consts c;
-};
-
+template <int NV>
 __global__ __launch_bounds__(kSetupThreads) void setup_kernel(SetupArgs a) {
-  __shared__ double sh[kSetupThreads];
-  __shared__ int ish[2];
-  const int tid = threadIdx.x;
-  const int q = a.q, nv = a.nv, N = nv - 1, n2 = 2 * nv, N1 = n2 + 6, N2 = nv + 6;
+  constexpr int N = NV - 1, n2 = 2 * NV, N1 = n2 + 6, N2 = NV + 6, T = kSetupThreads;
+  extern __shared__ __align__(16) double sm[];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int q = a.q;
   const Consts &c = a.c;
+  const SetupLds<NV> L(q);
+  double *P = sm + L.P, *Pd = sm + L.Pd, *Pdd = sm + L.Pdd, *U = sm + L.U, *V = sm + L.V, *W = sm + L.W;
+  double *R = sm + L.R, *Rinv = sm + L.Rinv, *G = sm + L.G, *bin = sm + L.bin;
 
-  // 1. Bernstein basis and its time derivatives on t_k = k tf/(q-1).
-  for (int idx = tid; idx < q * nv; idx += kSetupThreads) {
-    const int t = idx / nv, i = idx % nv;
-    const double tau = double(t) / double(q - 1);
-    c.P[idx] = bernstein(N, i, tau);
-    c.Pd[idx] = double(N) * (bernstein(N - 1, i - 1, tau) - bernstein(N - 1, i, tau)) / a.tf;
-    c.Pdd[idx] = double(N) * double(N - 1) *
-                 (bernstein(N - 2, i - 2, tau) - 2.0 * bernstein(N - 2, i - 1, tau) +
-                  bernstein(N - 2, i, tau)) / (a.tf * a.tf);
+  // 1. Binomials C(deg, i) (built multiplicatively, exact), then the Bernstein
+  //    basis and its time derivatives on t_k = k tf/(q-1).
+  if (tid < 3 * NV) {
+    const int deg = N - tid / NV, i = tid % NV;
+    double v = 1.0;
+    for (int k = 1; k <= i; ++k) v = v * double(deg - i + k) / double(k);
+    bin[tid] = i <= deg ? v : 0.0;
+    // (R is upper triangular)
   }
-  for (int idx = tid; idx < nv * nv; idx += kSetupThreads) c.R[idx] = 0.0;
+  for (int idx = tid; idx < NV * NV; idx += T) R[idx] = 0.0;
   __syncthreads();
-
-  // 2. Thin QR, P = U R, by Gram-Schmidt with one re-orthogonalisation pass.
-  for (int k = 0; k < nv; ++k) {
-    for (int t = tid; t < q; t += kSetupThreads) c.U[t * nv + k] = c.P[t * nv + k];
+  for (int idx = tid; idx < q * NV; idx += T) {
+    const int t = idx / NV, i = idx % NV;
+    const double tau = double(t) / double(q - 1);
+    const double p = bernstein(bin, N, i, tau);
+    const double pd = double(N) * (bernstein(bin + NV, N - 1, i - 1, tau) - bernstein(bin + NV, N - 1, i, tau)) / a.tf;
+    const double pdd = double(N) * double(N - 1) *
+                       (bernstein(bin + 2 * NV, N - 2, i - 2, tau) - 2.0 * bernstein(bin + 2 * NV, N - 2, i - 1, tau) +
+                        bernstein(bin + 2 * NV, N - 2, i, tau)) / (a.tf * a.tf);
+    P[idx] = p;
+    Pd[idx] = pd;
+    Pdd[idx] = pdd;
+    c.P[idx] = p;
+    c.Pd[idx] = pd;
+    c.Pdd[idx] = pdd;
+  }
+  __syncthreads();
+  // 2. Thin QR, P = U R, by Gram-Schmidt with one re-orthogonalisation pass:
+  //    all coefficients of a pass at once, one per wavefront.  (Loops are kept
+  //    rolled: unrolled code that runs once costs more in instruction
+  //    fetches than it saves.)
+  double *vcol = sm + L.vcol, *dj = sm + L.dj;
+#pragma unroll 1
+  for (int k = 0; k < NV; ++k) {
+    double *vc = vcol + (k & 1) * AM_MAX_Q;
+    double v = tid < q ? P[tid * NV + k] : 0.0;
+    if (tid < AM_MAX_Q) vc[tid] = v;
     __syncthreads();
-    for (int pass = 0; pass < 2; ++pass)
-      for (int j = 0; j < k; ++j) {
-        double part = 0.0;
-        for (int t = tid; t < q; t += kSetupThreads) part += c.U[t * nv + j] * c.U[t * nv + k];
-        const double rj = block_sum(part, sh);
-        for (int t = tid; t < q; t += kSetupThreads) c.U[t * nv + k] -= rj * c.U[t * nv + j];
-        if (tid == 0) c.R[j * nv + k] += rj;
+    if (k > 0) {
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+        for (int j = wave; j < k; j += T / kWave) {
+          const double x0 = lane < q ? U[lane * NV + j] : 0.0, x1 = lane + kWave < q ? U[(lane + kWave) * NV + j] : 0.0;
+          const double d = lane_sum(x0 * vc[lane] + x1 * vc[lane + kWave]);
+          if (lane == 0) {
+            dj[j] = d;
+            R[j * NV + k] += d;
+          }
+        }
+        __syncthreads();
+        if (tid < q) {
+#pragma unroll
+          for (int j = 0; j < NV - 1; ++j) {
+            const int jj = j < k ? j : 0;   // (the loads of all columns are issued together)
+            const double e = dj[jj] * U[tid * NV + jj];
+            v -= j < k ? e : 0.0;
+          }
+          vc[tid] = v;
+        }
         __syncthreads();
       }
-    double part = 0.0;
-    for (int t = tid; t < q; t += kSetupThreads) part += c.U[t * nv + k] * c.U[t * nv + k];
-    const double nrm = sqrt(block_sum(part, sh));
-    for (int t = tid; t < q; t += kSetupThreads) c.U[t * nv + k] /= nrm;
-    if (tid == 0) c.R[k * nv + k] = nrm;
-    __syncthreads();
-  }
-
-  // 3. R^-1 (upper triangular), column by column.
-  if (tid < nv) {
-    const int col = tid;
-    for (int i = nv - 1; i >= 0; --i) {
-      double s = (i == col) ? 1.0 : 0.0;
-      for (int j = i + 1; j < nv; ++j) s -= c.R[i * nv + j] * c.Rinv[j * nv + col];
-      c.Rinv[i * nv + col] = (i > col) ? 0.0 : s / c.R[i * nv + i];
     }
+    const double w0 = vc[lane], w1 = vc[lane + kWave];
+    const double nrm = sqrt(lane_sum(w0 * w0 + w1 * w1));
+    if (tid < q) U[tid * NV + k] = v / nrm;
+    if (tid == 0) R[k * NV + k] = nrm;
+  }
+  __syncthreads();
+  // 3. R^-1 (upper triangular), a column per lane of one wavefront.
+  if (tid < NV) {
+    double x[NV];
+#pragma unroll
+    for (int i = NV - 1; i >= 0; --i) {
+      double s = i == tid ? 1.0 : 0.0;
+#pragma unroll
+      for (int j = i + 1; j < NV; ++j) s -= R[i * NV + j] * x[j];
+      x[i] = i > tid ? 0.0 : s / R[i * NV + i];
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) Rinv[i * NV + tid] = x[i];
   }
   __syncthreads();
 
   // 4. V = Pdot R^-1, W = Pddot R^-1.
-  for (int idx = tid; idx < q * nv; idx += kSetupThreads) {
-    const int t = idx / nv, k = idx % nv;
+  for (int idx = tid; idx < q * NV; idx += T) {
+    const int t = idx / NV, k = idx % NV;
     double v = 0.0, w = 0.0;
-    for (int j = 0; j < nv; ++j) {
-      v += c.Pd[t * nv + j] * c.Rinv[j * nv + k];
-      w += c.Pdd[t * nv + j] * c.Rinv[j * nv + k];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      v += Pd[t * NV + j] * Rinv[j * NV + k];
+      w += Pdd[t * NV + j] * Rinv[j * NV + k];
     }
+    V[idx] = v;
+    W[idx] = w;
+    c.U[idx] = U[idx];
     c.V[idx] = v;
     c.W[idx] = w;
+  }
+  for (int idx = tid; idx < NV * NV; idx += T) {
+    c.R[idx] = R[idx];
+    c.Rinv[idx] = Rinv[idx];
   }
   __syncthreads();
 
   // 5. Gram matrices G_UU, G_VV, G_WW.
-  double *GUU = c.G, *GVV = c.G + nv * nv, *GWW = c.G + 2 * nv * nv;
-  for (int idx = tid; idx < 3 * nv * nv; idx += kSetupThreads) {
-    const int which = idx / (nv * nv), e = idx % (nv * nv), i = e / nv, j = e % nv;
-    const double *X = which == 0 ? c.U : (which == 1 ? c.V : c.W);
+  for (int idx = tid; idx < 3 * NV * NV; idx += T) {
+    const int which = idx / (NV * NV), e = idx % (NV * NV), i = e / NV, j = e % NV;
+    const double *X = which == 0 ? U : (which == 1 ? V : W);
     double s = 0.0;
-    for (int t = 0; t < q; ++t) s += X[t * nv + i] * X[t * nv + j];
+#pragma unroll 4
+    for (int t = 0; t < q; ++t) s += X[t * NV + i] * X[t * NV + j];
+    G[idx] = s;
     c.G[idx] = s;
   }
   __syncthreads();
 
-  // 6. F^T F of one axis and the two KKT matrices in z coordinates.
-  //    F rows: [V 0], [W 0], [U r_i U] per (i, j), [0 U]  (Sec. III-C).
+  // 6. F^T F of one axis inside the two KKT matrices in z coordinates,
+  //    augmented with the identity.  F rows: [V 0], [W 0], [U r_i U] per
+  //    (i, j), [0 U]  (Sec. III-C).
+  const double *GUU = G, *GVV = G + NV * NV, *GWW = G + 2 * NV * NV;
+  double *A1 = sm + L.A1, *A2 = sm + L.A2;
   double sr = 0.0, sr2 = 0.0;
   for (int i = 0; i < a.m; ++i) { sr += a.r[i]; sr2 += a.r[i] * a.r[i]; }
   const double mn = double(a.m) * double(a.n), nsr = double(a.n) * sr, nsr2 = double(a.n) * sr2;
   const bool q_cs = !(a.flags & AM_Q_CS_ZERO);
-  for (int idx = tid; idx < n2 * n2; idx += kSetupThreads) {
-    const int I = idx / n2, J = idx % n2, i = I % nv, j = J % nv;
-    const int bi = I / nv, bj = J / nv;
-    double f, qc;
-    if (bi == 0 && bj == 0) {
-      f = GVV[i * nv + j] + GWW[i * nv + j] + mn * GUU[i * nv + j];
-      qc = GWW[i * nv + j];
-    } else if (bi == 1 && bj == 1) {
-      f = (nsr2 + 1.0) * GUU[i * nv + j];
-      qc = q_cs ? GWW[i * nv + j] : 0.0;
-    } else {
-      f = nsr * GUU[i * nv + j];
-      qc = 0.0;
-    }
-    c.GF[idx] = f;
-    c.A1[I * 2 * N1 + J] = qc + a.rho * f;
-  }
-  // boundary rows: U, V, W at t = 0 and t = q-1 on the position block
-  for (int idx = tid; idx < 6 * N1; idx += kSetupThreads) {
-    const int e = idx / N1, J = idx % N1;
+  // boundary row e: U, V, W at t = 0 and t = q-1
+  auto brow = [&](int e, int k) {
+    const double *X = (e % 3 == 0) ? U : ((e % 3 == 1) ? V : W);
+    return X[(e < 3 ? 0 : q - 1) * NV + k];
+  };
+  constexpr int S1 = 2 * N1 + 1, S2 = 2 * N2 + 1;
+  for (int idx = tid; idx < N1 * 2 * N1; idx += T) {
+    const int I = idx / (2 * N1), J = idx % (2 * N1);
     double v = 0.0;
-    if (J < nv) {
-      const int t = e < 3 ? 0 : q - 1;
-      const double *X = (e % 3 == 0) ? c.U : ((e % 3 == 1) ? c.V : c.W);
-      v = X[t * nv + J];
+    if (J >= N1) {
+      v = J - N1 == I ? 1.0 : 0.0;
+    } else if (I < n2 && J < n2) {
+      const int i = I % NV, j = J % NV, bi = I / NV, bj = J / NV, e = i * NV + j;
+      if (bi == 0 && bj == 0) v = GWW[e] + a.rho * (GVV[e] + GWW[e] + mn * GUU[e]);
+      else if (bi == 1 && bj == 1) v = (q_cs ? GWW[e] : 0.0) + a.rho * ((nsr2 + 1.0) * GUU[e]);
+      else v = a.rho * (nsr * GUU[e]);
+    } else if (I < NV && J >= n2) {
+      v = brow(J - n2, I);   // column block A'^T
+    } else if (I >= n2 && J < NV) {
+      v = brow(I - n2, J);   // row block A'
     }
-    c.A1[(n2 + e) * 2 * N1 + J] = v;   // row block  A'
-    c.A1[J * 2 * N1 + n2 + e] = v;     // column block A'^T
+    A1[I * S1 + J] = v;
   }
-  for (int idx = tid; idx < 36; idx += kSetupThreads)
-    c.A1[(n2 + idx / 6) * 2 * N1 + n2 + idx % 6] = 0.0;
   // xi2: [W^T W + rho U^T U, A^T; A, 0]
-  for (int idx = tid; idx < N2 * N2; idx += kSetupThreads) {
-    const int I = idx / N2, J = idx % N2;
+  for (int idx = tid; idx < N2 * 2 * N2; idx += T) {
+    const int I = idx / (2 * N2), J = idx % (2 * N2);
     double v = 0.0;
-    if (I < nv && J < nv) v = GWW[I * nv + J] + a.rho * GUU[I * nv + J];
-    else if (I < nv || J < nv) {
-      const int e = (I < nv) ? J - nv : I - nv, k = (I < nv) ? I : J;
-      const int t = e < 3 ? 0 : q - 1;
-      const double *X = (e % 3 == 0) ? c.U : ((e % 3 == 1) ? c.V : c.W);
-      v = X[t * nv + k];
-    }
-    c.A2[I * 2 * N2 + J] = v;
+    if (J >= N2) v = J - N2 == I ? 1.0 : 0.0;
+    else if (I < NV && J < NV) v = GWW[I * NV + J] + a.rho * GUU[I * NV + J];
+    else if (I < NV) v = brow(J - NV, I);
+    else if (J < NV) v = brow(I - NV, J);
+    A2[I * S2 + J] = v;
   }
-  __syncthreads();
-  for (int idx = tid; idx < N1 * N1; idx += kSetupThreads)
-    c.K1[idx] = c.A1[(idx / N1) * 2 * N1 + idx % N1];
-  for (int idx = tid; idx < N2 * N2; idx += kSetupThreads)
-    c.K2[idx] = c.A2[(idx / N2) * 2 * N2 + idx % N2];
+  for (int idx = tid; idx < 6 * NV; idx += T) c.Abc[idx] = brow(idx / NV, idx % NV);
   __syncthreads();
 
-  // 7. Inverses.
-  const bool ok1 = gauss_jordan(c.A1, N1, sh, ish);
-  const bool ok2 = gauss_jordan(c.A2, N2, sh, ish);
-  if (tid == 0) c.status[0] = !ok1 ? 1.0 : (!ok2 ? 2.0 : 0.0);
+  // 7. Inverses, both matrices at once: half the wavefronts eliminate each.
+  //    A pivot is too small below 1e-13 of the largest entry.
+  const bool first = tid < T / 2;
+  const int gtid = first ? tid : tid - T / 2;
+  double *A = first ? A1 : A2;
+  const int NN = first ? N1 : N2, SS = first ? S1 : S2;
+  double big = 0.0;
+  for (int idx = lane; idx < NN * NN; idx += kWave) big = fmax(big, fabs(A[(idx / NN) * SS + idx % NN]));
+  big = wave_all(big, 0.0, [](double x, double y) { return fmax(x, y); });
+  const double tol = 1e-13 * big;
+  bool ok = big > 0.0;
+  double *from = A, *to = A + NN * SS;
+  for (int col = 0; col < N1; ++col) {
+    if (ok && col < NN) {
+      ok = first ? gj_step<N1, T / 2>(from, to, col, tol, gtid) : gj_step<N2, T / 2>(from, to, col, tol, gtid);
+      double *s = from;
+      from = to;
+      to = s;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) bin[0] = ok ? 0.0 : 1.0;
+  if (tid == T / 2) bin[1] = ok ? 0.0 : 2.0;
   __syncthreads();
-  if (!ok1 || !ok2) return;
+  const double status = bin[0] != 0.0 ? bin[0] : bin[1];
+  if (tid == 0) c.status[0] = status;
+  if (status != 0.0) return;
 
-  // 8. Blocks used by the iteration: [z; mu] = Kinv [rhs; b].
-  for (int idx = tid; idx < n2 * n2; idx += kSetupThreads)
-    c.M1[idx] = c.A1[(idx / n2) * 2 * N1 + N1 + idx % n2];
-  for (int idx = tid; idx < n2 * 6; idx += kSetupThreads)
-    c.H1[idx] = c.A1[(idx / 6) * 2 * N1 + N1 + n2 + idx % 6];
-  for (int idx = tid; idx < nv * nv; idx += kSetupThreads)
-    c.M2[idx] = c.A2[(idx / nv) * 2 * N2 + N2 + idx % nv];
-  for (int idx = tid; idx < nv * 6; idx += kSetupThreads)
-    c.H2[idx] = c.A2[(idx / 6) * 2 * N2 + N2 + nv + idx % 6];
-  // Bernstein-coordinate inverses T Kinv T^T with T = blkdiag(R^-1, ..., I6).
-  for (int idx = tid; idx < N1 * N1; idx += kSetupThreads) {
-    const int I = idx / N1, J = idx % N1;
-    double s = 0.0;
-    for (int k = 0; k < N1; ++k) {
-      const double tik = (I < n2) ? ((k < n2 && k / nv == I / nv) ? c.Rinv[(I % nv) * nv + k % nv] : 0.0)
-                                  : (k == I ? 1.0 : 0.0);
-      if (tik == 0.0) continue;
-      for (int l = 0; l < N1; ++l) {
-        const double tjl = (J < n2) ? ((l < n2 && l / nv == J / nv) ? c.Rinv[(J % nv) * nv + l % nv] : 0.0)
-                                    : (l == J ? 1.0 : 0.0);
-        if (tjl != 0.0) s += tik * c.A1[k * 2 * N1 + N1 + l] * tjl;
+  // 8. The inverses, and the blocks used by the iteration: [z; mu] = Kinv
+  //    [rhs; b].
+  for (int idx = gtid; idx < NN * NN; idx += T / 2) {
+    const int I = idx / NN, J = idx % NN;
+    const double v = from[I * SS + NN + J];
+    if (first) {
+      c.K1[idx] = v;
+      if (I < n2 && J < n2) c.M1[I * n2 + J] = v;
+      else if (I < n2) c.H1[I * 6 + J - n2] = v;
+    } else {
+      c.K2[idx] = v;
+      if (I < NV && J < NV) c.M2[I * NV + J] = v;
+      else if (I < NV) c.H2[I * 6 + J - NV] = v;
+    }
+  }
+}
+
+// What only depends on the first kernel's results: one job per blockIdx.y,
+// an entry per thread.
+constexpr int kPackJobs = 13;
+
+template <int NV, typename F>
+__global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
+  constexpr int n2 = 2 * NV, N1 = n2 + 6, N2 = NV + 6;
+  const Consts &c = a.c;
+  const int q = a.q, job = blockIdx.y, qn = q * NV;
+  const int tid = blockIdx.x * kPackThreads + threadIdx.x, T = kPackBlocks * kPackThreads;
+  const bool q_cs = !(a.flags & AM_Q_CS_ZERO);
+  const double *GWW = c.G + 2 * NV * NV;
+  // Bernstein-coordinate inverses T Kinv T^T with T = blkdiag(R^-1, ..., I6):
+  // row I of T runs over the block of I (nz rows of such blocks)
+  auto bernstein_inv = [&](const double *K, double *out, int n, int nz) {
+    for (int idx = tid; idx < n * n; idx += T) {
+      const int I = idx / n, J = idx % n;
+      const bool bi = I < nz, bj = J < nz;
+      const int k0 = bi ? I / NV * NV : I, l0 = bj ? J / NV * NV : J;
+      double tj[NV], s = 0.0;
+#pragma unroll
+      for (int l = 0; l < NV; ++l) tj[l] = bj ? c.Rinv[(J % NV) * NV + l] : (l == 0 ? 1.0 : 0.0);
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const double ti = bi ? c.Rinv[(I % NV) * NV + k] : (k == 0 ? 1.0 : 0.0);
+        double row = 0.0;
+#pragma unroll
+        for (int l = 0; l < NV; ++l) row += K[(bi ? k0 + k : k0) * n + (bj ? l0 + l : l0)] * tj[l];
+        s += ti * row;
       }
+      out[idx] = s;
     }
-    c.K1b_inv[idx] = s;
-  }
-  for (int idx = tid; idx < N2 * N2; idx += kSetupThreads) {
-    const int I = idx / N2, J = idx % N2;
-    double s = 0.0;
-    for (int k = 0; k < N2; ++k) {
-      const double tik = (I < nv) ? (k < nv ? c.Rinv[I * nv + k] : 0.0) : (k == I ? 1.0 : 0.0);
-      if (tik == 0.0) continue;
-      for (int l = 0; l < N2; ++l) {
-        const double tjl = (J < nv) ? (l < nv ? c.Rinv[J * nv + l] : 0.0) : (l == J ? 1.0 : 0.0);
-        if (tjl != 0.0) s += tik * c.A2[k * 2 * N2 + N2 + l] * tjl;
-      }
+  };
+  if (job == 0) {
+    bernstein_inv(c.K1, c.K1b_inv, N1, n2);
+  } else if (job == 1) {
+    bernstein_inv(c.K2, c.K2b_inv, N2, NV);
+  } else if (job == 2) {
+    // U~ = U M2^T: the heading step's rows premultiplied by M2
+    for (int idx = tid; idx < qn; idx += T) {
+      const int t = idx / NV, k = idx % NV;
+      double v = 0.0;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) v += c.U[t * NV + j] * c.M2[k * NV + j];
+      static_cast<F *>(c.tUt)[idx] = F(v);
     }
-    c.K2b_inv[idx] = s;
-  }
-  __syncthreads();
-
-  // N = M1 Q with Q the smoothness block of the xi1 objective (the same
-  // blocks as in A1); boundary rows of the position block in the z basis
-  for (int idx = tid; idx < n2 * n2; idx += kSetupThreads) {
-    const int I = idx / n2, J = idx % n2, bj = J / nv, j = J % nv;
-    double v = 0.0;
-    if (bj == 0 || q_cs)
-      for (int k = 0; k < nv; ++k) v += c.M1[I * n2 + bj * nv + k] * GWW[k * nv + j];
-    c.N[idx] = v;
-  }
-  for (int idx = tid; idx < 6 * nv; idx += kSetupThreads) {
-    const int e = idx / nv, k = idx % nv, t = e < 3 ? 0 : q - 1;
-    const double *X = (e % 3 == 0) ? c.U : ((e % 3 == 1) ? c.V : c.W);
-    c.Abc[idx] = X[t * nv + k];
-  }
-  // U~ = U M2^T: the heading step's rows premultiplied by M2
-  for (int idx = tid; idx < q * nv; idx += kSetupThreads) {
-    const int t = idx / nv, k = idx % nv;
-    double v = 0.0;
-    for (int j = 0; j < nv; ++j) v += c.U[t * nv + j] * c.M2[k * nv + j];
-    c.Ut[idx] = v;
-  }
-  __syncthreads();
-
-  // 9. Typed copies for the iteration kernels.
-  if (a.f64) {
-    to_typed<double>(c.U, c.tU, q * nv); to_typed<double>(c.V, c.tV, q * nv);
-    to_typed<double>(c.W, c.tW, q * nv); to_typed<double>(c.M1, c.tM1, n2 * n2);
-    to_typed<double>(c.H1, c.tH1, n2 * 6); to_typed<double>(c.M2, c.tM2, nv * nv);
-    to_typed<double>(c.H2, c.tH2, nv * 6); to_typed<double>(c.GF, c.tGF, n2 * n2);
-    to_typed<double>(c.P, c.tP, q * nv); to_typed<double>(c.Pd, c.tPd, q * nv);
-    to_typed<double>(c.Pdd, c.tPdd, q * nv); to_typed<double>(c.Ut, c.tUt, q * nv);
-    to_typed<double>(c.N, c.tN, n2 * n2);
+  } else if (job == 3) {
+    // N = M1 Q with Q the smoothness block of the xi1 objective
+    for (int idx = tid; idx < n2 * n2; idx += T) {
+      const int I = idx / n2, J = idx % n2, bj = J / NV, j = J % NV;
+      double v = 0.0;
+      if (bj == 0 || q_cs)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) v += c.M1[I * n2 + bj * NV + k] * GWW[k * NV + j];
+      static_cast<F *>(c.tN)[idx] = F(v);
+    }
   } else {
-    to_typed<float>(c.U, c.tU, q * nv); to_typed<float>(c.V, c.tV, q * nv);
-    to_typed<float>(c.W, c.tW, q * nv); to_typed<float>(c.M1, c.tM1, n2 * n2);
-    to_typed<float>(c.H1, c.tH1, n2 * 6); to_typed<float>(c.M2, c.tM2, nv * nv);
-    to_typed<float>(c.H2, c.tH2, nv * 6); to_typed<float>(c.GF, c.tGF, n2 * n2);
-    to_typed<float>(c.P, c.tP, q * nv); to_typed<float>(c.Pd, c.tPd, q * nv);
-    to_typed<float>(c.Pdd, c.tPdd, q * nv); to_typed<float>(c.Ut, c.tUt, q * nv);
-    to_typed<float>(c.N, c.tN, n2 * n2);
+    // typed copies
+    const double *const src[] = {c.U, c.V, c.W, c.P, c.Pd, c.Pdd, c.M1, c.M2, c.H2};
+    void *const dst[] = {c.tU, c.tV, c.tW, c.tP, c.tPd, c.tPdd, c.tM1, c.tM2, c.tH2};
+    const int count[] = {qn, qn, qn, qn, qn, qn, n2 * n2, NV * NV, NV * 6};
+    static_assert(sizeof(count) / sizeof(count[0]) == kPackJobs - 4, "a job per copy");
+#pragma unroll
+    for (int k = 0; k < kPackJobs - 4; ++k)
+      if (job == 4 + k)
+        for (int i = tid; i < count[k]; i += T) static_cast<F *>(dst[k])[i] = F(src[k][i]);
   }
+}
+
+template <int NV>
+hipError_t run(const SetupArgs &a, hipStream_t st) {
+  const size_t lds = size_t(SetupLds<NV>(a.q).total) * sizeof(double);
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&setup_kernel<NV>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((setup_kernel<NV>), dim3(1), dim3(kSetupThreads), lds, st, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (a.f64) hipLaunchKernelGGL((pack_kernel<NV, double>), dim3(kPackBlocks, kPackJobs), dim3(kPackThreads), 0, st, a);
+  else hipLaunchKernelGGL((pack_kernel<NV, float>), dim3(kPackBlocks, kPackJobs), dim3(kPackThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_setup(const am_shape &s, const double *r_dev, const Consts &c, bool f64,
-                        hipStream_t st) {
-  SetupArgs a;
-  a.q = s.q; a.nv = s.nv; a.m = s.m; a.n = s.n_obs; a.flags = int(s.flags); a.f64 = f64 ? 1 : 0;
-  a.tf = s.tf; a.rho = s.rho; a.r = r_dev; a.c = c;
-  hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(kSetupThreads), 0, st, a);
-  return hipGetLastError();
+hipError_t launch_setup(const am_shape &s, const double *r, const Consts &c, bool f64, hipStream_t st) {
+  SetupArgs a{};
+  a.q = s.q; a.m = s.m; a.n = s.n_obs; a.flags = int(s.flags); a.f64 = f64 ? 1 : 0;
+  a.tf = s.tf; a.rho = s.rho; a.c = c;
+  for (int i = 0; i < s.m; ++i) a.r[i] = r[i];
+  if (s.nv == 11) return run<11>(a, st);
+  if (s.nv == 8) return run<8>(a, st);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace amk
