@@ -169,6 +169,26 @@ struct alignas(4 * sizeof(T)) Quad {
   T a, b, c, d;
 };
 
+// What a lane of the fused kernel holds of a handle's constants, laid out so
+// that a wavefront reads each 16-byte piece of all lanes in one coalesced
+// access.  Quads of T [piece][64 lanes]: per half its slots of the basis rows
+// U, V, W and U~ (pad4(nv) values each, zero where there is no time step),
+// then for both halves row I of M1, its row of Q, row `lane` of M2 and of H2.
+// Pairs of double [piece][64]: per half the row of U at its time step, then
+// the row of H1, the row of W^T W, row and column kk = I mod nv of R and
+// R^-1, and (lanes 0..11) boundary row lane mod 6.
+__host__ __device__ constexpr int lane_t_half(int nv) { return pad4(nv); }
+__host__ __device__ constexpr int lane_t_m1(int nv) { return 2 * lane_t_half(nv); }
+__host__ __device__ constexpr int lane_t_q(int nv) { return lane_t_m1(nv) + pad4(2 * nv) / 4; }
+__host__ __device__ constexpr int lane_t_m2(int nv) { return lane_t_q(nv) + pad4(nv) / 4; }
+__host__ __device__ constexpr int lane_t_h2(int nv) { return lane_t_m2(nv) + pad4(nv) / 4; }
+__host__ __device__ constexpr int lane_t_quads(int nv) { return (lane_t_h2(nv) + 2) * kWave; }
+// pieces of nv doubles (padded to pad4(nv)) after the two halves' U and H1
+enum { LD_Q = 0, LD_R_ROW, LD_RINV_COL, LD_RINV_ROW, LD_R_COL, LD_ABC, LD_PIECES };
+__host__ __device__ constexpr int lane_d_h1(int nv) { return pad4(nv); }
+__host__ __device__ constexpr int lane_d_piece(int nv, int k) { return lane_d_h1(nv) + 3 + k * pad4(nv) / 2; }
+__host__ __device__ constexpr int lane_d_pairs(int nv) { return lane_d_piece(nv, LD_PIECES) * kWave; }
+
 // LDS carve-up of the fused kernel, in elements of T.  Offsets are multiples
 // of 8 elements, so Pair and Quad reads (and FP64 pairs when T is float)
 // are aligned.

@@ -256,112 +256,126 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   s1 *= T(n);   // n sum r_i
   s2 *= T(n);   // n sum r_i^2
 
-  // ---- per-lane basis rows (constant for the whole solve), U~ = U M2^T
-  const T *gU = static_cast<const T *>(Dsrc.U), *gV = static_cast<const T *>(Dsrc.V),
-          *gW = static_cast<const T *>(Dsrc.W), *gUt = static_cast<const T *>(Dsrc.Ut),
-          *gM2 = static_cast<const T *>(Dsrc.M2);
-  // (in this lane's slot order; rows past nv are zero)
+  // ---- initial state: lane I of the position block takes its coefficient
+  // and multiplier, lane k of the heading block the heading's, staged in LDS
+  // (rows NP apart) for the changes of basis below.  One load per lane and
+  // array: a lane that reads its whole rows itself keeps the address units
+  // busy for longer than everything else here takes.
+  const int blk = axis * 2 + (I >= NV), kk = I % NV;   // (kk is also the heading row of lanes < nv)
+  const double coff = (blk == 0) ? offx : ((blk == 2) ? offy : 0.0);
+  double c0 = 0.0, l0 = 0.0, cp0 = 0.0, lp0 = 0.0;
+  if (prow) {
+    const T *src = static_cast<const T *>(blk == 0 ? Dsrc.cx : (blk == 1 ? Dsrc.cc : (blk == 2 ? Dsrc.cy : Dsrc.cs)));
+    c0 = double(src[size_t(l) * NV + kk]);
+    l0 = double(static_cast<const T *>(Dsrc.lam)[size_t(l) * 4 * NV + lane]);
+  }
+  if (hrow) {
+    cp0 = double(static_cast<const T *>(Dsrc.cpsi)[size_t(l) * NV + lane]);
+    lp0 = double(static_cast<const T *>(Dsrc.lampsi)[size_t(l) * NV + lane]);
+  }
+  // ---- this lane's constants: its slots of the basis rows (zero past nv and
+  // off the time grid), its rows of the operators
+  const Quad<T> *lt = static_cast<const Quad<T> *>(Dsrc.lane_t) + lane;
+  const Pair<double> *ld = reinterpret_cast<const Pair<double> *>(Dsrc.lane_d) + lane;
   T Ub[NP], Vb[NP], Wb[NP], Ut[NP];
 #pragma unroll
-  for (int k = 0; k < NP; ++k) {
-    const int r = (k & ~3) | ((k & 3) ^ sq);
-    const bool use = tv && r < NV;
-    const int e = use ? tt * NV + r : 0;
-    Ub[k] = use ? gU[e] : T(0);
-    Vb[k] = use ? gV[e] : T(0);
-    Wb[k] = use ? gW[e] : T(0);
-    Ut[k] = use ? gUt[e] : T(0);
+  for (int k = 0; k < NP / 4; ++k) {
+    auto slots = [&](T *v, int which) {
+      const Quad<T> x = lt[(half * NP + which * (NP / 4) + k) * kWave];
+      v[4 * k] = x.a; v[4 * k + 1] = x.b; v[4 * k + 2] = x.c; v[4 * k + 3] = x.d;
+    };
+    slots(Ub, 0);
+    slots(Vb, 1);
+    slots(Wb, 2);
+    slots(Ut, 3);
   }
+  double h1r[6], udr[NP], qdr[NP], rrow[NP], ricol[NP], abc[NP];
+  T m2r[NP], h2r[8];
+  auto pairs = [&](double *v, int at, int count) {
+#pragma unroll
+    for (int k = 0; k < count; ++k) {
+      const Pair<double> x = ld[(at + k) * kWave];
+      v[2 * k] = x.x;
+      v[2 * k + 1] = x.y;
+    }
+  };
+  auto quads = [&](T *v, int at, int count) {
+#pragma unroll
+    for (int k = 0; k < count; ++k) {
+      const Quad<T> x = lt[(at + k) * kWave];
+      v[4 * k] = x.a; v[4 * k + 1] = x.b; v[4 * k + 2] = x.c; v[4 * k + 3] = x.d;
+    }
+  };
+  pairs(rrow, lane_d_piece(NV, LD_R_ROW), NP / 2);
+  pairs(ricol, lane_d_piece(NV, LD_RINV_COL), NP / 2);
+  pairs(abc, lane_d_piece(NV, LD_ABC), NP / 2);
+  pairs(h1r, lane_d_h1(NV), 3);
+  pairs(udr, half * (NP / 2), NP / 2);
+  pairs(qdr, lane_d_piece(NV, LD_Q), NP / 2);
+  quads(m2r, lane_t_m2(NV), NP / 4);
+  quads(h2r, lane_t_h2(NV), 2);
 
-  // ---- boundary terms h = H b (centred positions) and the initial state
-  const double *R = Dsrc.R, *Rinv = Dsrc.Rinv;
   // lane I of the position block: its coefficient, multiplier and the
   // boundary correction of the first update, in FP64
   double zl = 0.0, lam = 0.0, bcc = 0.0;
   T hpsi = T(0), lampsi0 = T(0);
-  // rows of the set-up operators this lane uses after the LDS exchanges
-  // below (H1, M2, the FP64 rows of U and Q), loaded first so that their
-  // latency overlaps that of the state loads
-  double h1r[6], udr[NV], qdr[NV];
-  T m2r[NV];
-  {
-    const int ih = prow ? I : 0, iu = tv ? tt : 0, iq = prow ? I % NV : 0, im = hrow ? lane : 0;
-#pragma unroll
-    for (int e = 0; e < 6; ++e) h1r[e] = Dsrc.H1d[ih * 6 + e];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      udr[k] = Dsrc.Ud[iu * NV + k];
-      qdr[k] = Dsrc.Qd[iq * NV + k];
-      m2r[k] = gM2[im * NV + k];
-    }
-  }
+  double *st = reinterpret_cast<double *>(red);   // [10][NP]: cx cc cy cs cpsi, their multipliers
   if (prow) {
-    // z = R (c - off): the basis reproduces constants, so shifting all
-    // coefficients of a position shifts its curve
-    const int b = axis * 2 + (I >= NV), kk = I % NV;
-    const T *src = static_cast<const T *>(b == 0 ? Dsrc.cx : (b == 1 ? Dsrc.cc : (b == 2 ? Dsrc.cy : Dsrc.cs)));
-    const double coff = (b == 0) ? offx : ((b == 2) ? offy : 0.0);
-    // (the set-up loops run over all NV entries with the unused terms
-    // selected away, so that each lane's loads are issued together; the
-    // sums keep their order)
-    double zz = 0.0;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const double t = R[kk * NV + j] * (double(src[size_t(l) * NV + j]) - coff);
-      zz += j >= kk ? t : 0.0;
-    }
-    zl = zz;
-    vzd[axis * A2 + I] = zz;
-    // (z itself goes through the dz copies for the first evaluation)
-    put4(vdz, DZC, axis * A2 + (I / NV) * QS + I % NV, T(zz));
-    // lambda_z = R^-T lambda
-    const T *glam = static_cast<const T *>(Dsrc.lam);
-    double lz = 0.0;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const double t = Rinv[j * NV + kk] * double(glam[size_t(l) * 4 * NV + b * NV + j]);
-      lz += j <= kk ? t : 0.0;
-    }
-    lam = lz;
+    // (centred positions: the basis reproduces constants, so shifting all
+    // coefficients of a position shifts its curve)
+    st[blk * NP + kk] = c0 - coff;
+    st[(5 + blk) * NP + kk] = l0;
   }
   if (hrow) {
-    const int kk = lane;
-    const T *H2 = static_cast<const T *>(Dsrc.H2);
-    double hsum = 0.0;
-#pragma unroll
-    for (int e = 0; e < 6; ++e) hsum += double(H2[kk * 6 + e]) * Dsrc.bpsi[e];
-    hpsi = T(hsum);
-    const T *src = static_cast<const T *>(Dsrc.cpsi);
-    double zz = 0.0;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const double t = R[kk * NV + j] * double(src[size_t(l) * NV + j]);
-      zz += j >= kk ? t : 0.0;
-    }
-    put4(vzpsi, ZPC, kk, T(zz));
-    const T *glp = static_cast<const T *>(Dsrc.lampsi);
-    double lz = 0.0;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const double t = Rinv[j * NV + kk] * double(glp[size_t(l) * NV + j]);
-      lz += j <= kk ? t : 0.0;
-    }
-    lampsi0 = T(lz);
-    vaux[kk] = lampsi0;
+    st[4 * NP + lane] = cp0;
+    st[9 * NP + lane] = lp0;
   }
   wave_sync();
-  // H1 (A z - b) of the given coefficients (centred positions)
-  if (prow) {
-    const double *bb = axis == 0 ? Dsrc.bx : Dsrc.by;
-    const double off = axis == 0 ? offx : offy;
+  // z = R c and lambda_z = R^-T lambda (unused terms selected away, so that
+  // the loops have no lane-dependent bounds)
+  auto basis_change = [&](int row, double &z, double &lz) {
+    double zz = 0.0, ll = 0.0;
 #pragma unroll
-    for (int e = 0; e < 6; ++e) {
-      double ae = 0.0;
-#pragma unroll
-      for (int k = 0; k < NV; ++k) ae += Dsrc.Abc[e * NV + k] * vzd[axis * A2 + k];
-      const double be = (e == 0 || e == 3) ? bb[e] - off : bb[e];
-      bcc += h1r[e] * (ae - be);
+    for (int j = 0; j < NV; ++j) {
+      const double t = rrow[j] * st[row * NP + j], u = ricol[j] * st[(5 + row) * NP + j];
+      zz += j >= kk ? t : 0.0;
+      ll += j <= kk ? u : 0.0;
     }
+    z = zz;
+    lz = ll;
+  };
+  if (prow) {
+    basis_change(blk, zl, lam);
+    vzd[axis * A2 + I] = zl;
+    // (z itself goes through the dz copies for the first evaluation)
+    put4(vdz, DZC, axis * A2 + (I / NV) * QS + I % NV, T(zl));
+  }
+  if (hrow) {
+    double hsum = 0.0, zz, lz;
+#pragma unroll
+    for (int e = 0; e < 6; ++e) hsum += double(h2r[e]) * Dsrc.bpsi[e];
+    hpsi = T(hsum);
+    basis_change(4, zz, lz);
+    put4(vzpsi, ZPC, lane, T(zz));
+    lampsi0 = T(lz);
+    vaux[lane] = lampsi0;
+  }
+  wave_sync();
+  // A z - b of the given coefficients (centred positions), a row per lane,
+  // then H1 (A z - b)
+  if (lane < 12) {
+    const int e = lane % 6, ax = lane / 6;
+    const double off = ax == 0 ? offx : offy;
+    double ae = 0.0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) ae += abc[k] * vzd[ax * A2 + k];
+    const double be = ax == 0 ? Dsrc.bx[e] : Dsrc.by[e];
+    st[lane] = ae - ((e == 0 || e == 3) ? be - off : be);
+  }
+  wave_sync();
+  if (prow) {
+#pragma unroll
+    for (int e = 0; e < 6; ++e) bcc += h1r[e] * st[axis * 6 + e];
   }
   // mu = M2 lambda_psi (heading rows)
   T mu = T(0);
@@ -735,9 +749,8 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   constexpr int M1Q = pad4(N2) / 4;
   Quad<T> m1r[RED == kRedRows ? M1Q : 1];
   if constexpr (RED == kRedRows) {
-    const Quad<T> *o = reinterpret_cast<const Quad<T> *>(M1);
 #pragma unroll
-    for (int c = 0; c < M1Q; ++c) m1r[c] = o[c * N2 + I];
+    for (int c = 0; c < M1Q; ++c) m1r[c] = lt[(lane_t_m1(NV) + c) * kWave];
   }
   auto m1_dot = [&](const T *v) -> T {
     if constexpr (RED == kRedRows) {
@@ -762,9 +775,8 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   // (in registers under the two-wavefront budget, like the M1 row)
   Quad<T> qr[RED == kRedRows ? QS / 4 : 1];
   if constexpr (RED == kRedRows) {
-    const Quad<T> *o = reinterpret_cast<const Quad<T> *>(QL + (qb * NV + qi) * QS);
 #pragma unroll
-    for (int c = 0; c < QS / 4; ++c) qr[c] = o[c];
+    for (int c = 0; c < QS / 4; ++c) qr[c] = lt[(lane_t_q(NV) + c) * kWave];
   }
   auto q_dot = [&]() {
     const Quad<T> *o = reinterpret_cast<const Quad<T> *>(QL + (qb * NV + qi) * QS);
@@ -978,33 +990,33 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   if (!live) return;   // padding trajectory of a ragged last block
 
   // ---- state back to Bernstein coordinates (written by the first half)
-  if (half == 0) {
+  if (half == 0 && (prow || hrow)) {
+    double rirow[NP], rcol[NP];
+    pairs(rirow, lane_d_piece(NV, LD_RINV_ROW), NP / 2);
+    pairs(rcol, lane_d_piece(NV, LD_R_COL), NP / 2);
     if (prow) {
-      const int b = axis * 2 + (I >= NV), kk = I % NV;
-      T *dst = static_cast<T *>(b == 0 ? Dsrc.cx : (b == 1 ? Dsrc.cc : (b == 2 ? Dsrc.cy : Dsrc.cs)));
-      const double coff = (b == 0) ? offx : ((b == 2) ? offy : 0.0);
+      T *dst = static_cast<T *>(blk == 0 ? Dsrc.cx : (blk == 1 ? Dsrc.cc : (blk == 2 ? Dsrc.cy : Dsrc.cs)));
       const int base = axis * A2 + (I >= NV ? NV : 0);
       double c = 0.0, lc = 0.0;
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
-        const double t = Rinv[kk * NV + j] * vzd[base + j], u = R[j * NV + kk] * vwd[base + j];
+        const double t = rirow[j] * vzd[base + j], u = rcol[j] * vwd[base + j];
         c += j >= kk ? t : 0.0;
         lc += j <= kk ? u : 0.0;
       }
       dst[size_t(l) * NV + kk] = T(c + coff);
-      static_cast<T *>(Dsrc.lam)[size_t(l) * 4 * NV + b * NV + kk] = T(lc);
+      static_cast<T *>(Dsrc.lam)[size_t(l) * 4 * NV + lane] = T(lc);
     }
     if (hrow) {
-      const int kk = lane;
       double c = 0.0, lc = 0.0;
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
-        const double t = Rinv[kk * NV + j] * double(vzpsi[j]), u = R[j * NV + kk] * double(vaux[2 * A2 + j]);
+        const double t = rirow[j] * double(vzpsi[j]), u = rcol[j] * double(vaux[2 * A2 + j]);
         c += j >= kk ? t : 0.0;
         lc += j <= kk ? u : 0.0;
       }
-      static_cast<T *>(Dsrc.cpsi)[size_t(l) * NV + kk] = T(c);
-      static_cast<T *>(Dsrc.lampsi)[size_t(l) * NV + kk] = T(lc);
+      static_cast<T *>(Dsrc.cpsi)[size_t(l) * NV + lane] = T(c);
+      static_cast<T *>(Dsrc.lampsi)[size_t(l) * NV + lane] = T(lc);
     }
   }
   if (!tv) return;
@@ -1063,7 +1075,18 @@ __device__ __forceinline__ void fused_block(const Desc &D) {
   const T *gox = static_cast<const T *>(D.ox), *goy = static_cast<const T *>(D.oy);
   const T rc = T(D.rc);
   Pair<T> *oxy = reinterpret_cast<Pair<T> *>(lds + L.oxy);
-  for (int i = tid; i < n * q; i += blockDim.x) oxy[i] = Pair<T>{gox[i], goy[i]};
+  constexpr int BD = kWave * 2 * TILE, kFill = 4;   // (kFill entries per thread in flight)
+  for (int i0 = tid; i0 < n * q; i0 += kFill * BD) {
+    Pair<T> v[kFill];
+#pragma unroll
+    for (int k = 0; k < kFill; ++k) {
+      const int i = i0 + k * BD < n * q ? i0 + k * BD : i0;
+      v[k] = Pair<T>{gox[i], goy[i]};
+    }
+#pragma unroll
+    for (int k = 0; k < kFill; ++k)
+      if (i0 + k * BD < n * q) oxy[i0 + k * BD] = v[k];
+  }
   for (int j = tid; j < n; j += blockDim.x) {
     const T a = static_cast<const T *>(D.oa)[j] + rc;
     const T b = static_cast<const T *>(D.ob)[j] + rc;
@@ -1071,20 +1094,14 @@ __device__ __forceinline__ void fused_block(const Desc &D) {
     o[OP_A2] = a * a; o[OP_B2] = b * b; o[OP_AB] = a * b; o[OP_AMAX] = fmax(a, b);
     o[OP_A] = a; o[OP_B] = b; o[OP_IA2] = T(1) / (a * a); o[OP_IB2] = T(1) / (b * b);
   }
-  const T *gM1 = static_cast<const T *>(D.M1);
-  for (int e = tid; e < A2 * N2; e += blockDim.x) {
-    // element e of the Quad layout: chunk c, row I, component e % 4
-    const int c = e / (4 * N2), rem = e % (4 * N2), I = rem / 4, J = 4 * c + rem % 4;
-    lds[L.m1 + e] = J < N2 ? gM1[I * N2 + J] : T(0);
-  }
-  // Q rows: [block][row][pad4(nv)], the slack block zero under AM_Q_CS_ZERO
-  {
-    constexpr int QS = pad4(NV);
-    const bool qcs = !(uni(D.flags) & AM_Q_CS_ZERO);
-    for (int e = tid; e < 2 * NV * QS; e += blockDim.x) {
-      const int bq = e / (NV * QS), rem = e % (NV * QS), i = rem / QS, k = rem % QS;
-      lds[L.qrows + e] = (k < NV && (bq == 0 || qcs)) ? T(D.Qd[i * NV + k]) : T(0);
-    }
+  // (under the two-wavefront budget each lane holds its rows of M1 and Q)
+  if constexpr (RED != kRedRows) {
+    const Quad<T> *lt = static_cast<const Quad<T> *>(D.lane_t);
+    Quad<T> *m1 = reinterpret_cast<Quad<T> *>(lds + L.m1), *ql = reinterpret_cast<Quad<T> *>(lds + L.qrows);
+    for (int e = tid; e < A2 / 4 * N2; e += blockDim.x) m1[e] = lt[(lane_t_m1(NV) + e / N2) * kWave + e % N2];
+    // Q rows: [block][row][pad4(nv)], the slack block zero under AM_Q_CS_ZERO
+    constexpr int QC = pad4(NV) / 4;
+    for (int e = tid; e < N2 * QC; e += blockDim.x) ql[e] = lt[(lane_t_q(NV) + e % QC) * kWave + e / QC];
   }
   // (the reduction scratch at the end of each wave's area is written before
   // it is read and is left as it is)

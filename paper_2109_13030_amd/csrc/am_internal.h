@@ -27,12 +27,12 @@ struct Desc {
   const void *M1;            // xi1: [2nv][2nv]
   const void *M2, *H2;       // xi2: [nv][nv] and [nv][6]
   const void *N;             // [2nv][2nv] M1 Q (Q: smoothness cost of one axis in the z basis)
-  const void *Ut;            // [q][nv] U M2^T (heading rows premultiplied by M2)
   const double *R, *Rinv;    // z = R c (Bernstein c), [nv][nv]
   const double *Ud;          // [q][nv] U in FP64 (positions)
   const double *Abc;         // [6][nv] boundary rows U, V, W at t = 0 and t = q-1 (z basis)
   const double *H1d;         // [2nv][6] H1 in FP64
-  const double *Qd;          // [nv][nv] W^T W in the z basis (FP64): the smoothness block of Q
+  const void *lane_t;        // the fused kernel's lanes' constants, T (see lane_t_half)
+  const double *lane_d;      // ... and FP64
   // problem
   const void *ox, *oy, *oa, *ob;
   // state (Bernstein coordinates at the boundary)
@@ -63,6 +63,8 @@ struct Consts {
   void *tU, *tV, *tW, *tM1, *tM2, *tH2;   // typed copies
   void *tP, *tPd, *tPdd;
   void *tUt, *tN;                // U M2^T and M1 Q, typed
+  void *lane_t;                  // lanes' constants of the fused kernel, typed
+  double *lane_d;                // ... and FP64
 };
 
 // Launchers (defined in the .hip files).

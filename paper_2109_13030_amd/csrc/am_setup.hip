@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(SetupArgs a) {
 
 // What only depends on the first kernel's results: one job per blockIdx.y,
 // an entry per thread.
-constexpr int kPackJobs = 13;
+constexpr int kPackJobs = 15;
 
 template <int NV, typename F>
 __global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
@@ -365,19 +365,21 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
       out[idx] = s;
     }
   };
+  // row t, column k of U~ = U M2^T: the heading step's rows premultiplied by M2
+  auto ut_of = [&](int t, int k) {
+    double v = 0.0;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v += c.U[t * NV + j] * c.M2[k * NV + j];
+    return v;
+  };
+  const int hq = (q + 1) / 2;
+  constexpr int NP = pad4(NV);
   if (job == 0) {
     bernstein_inv(c.K1, c.K1b_inv, N1, n2);
   } else if (job == 1) {
     bernstein_inv(c.K2, c.K2b_inv, N2, NV);
   } else if (job == 2) {
-    // U~ = U M2^T: the heading step's rows premultiplied by M2
-    for (int idx = tid; idx < qn; idx += T) {
-      const int t = idx / NV, k = idx % NV;
-      double v = 0.0;
-#pragma unroll
-      for (int j = 0; j < NV; ++j) v += c.U[t * NV + j] * c.M2[k * NV + j];
-      static_cast<F *>(c.tUt)[idx] = F(v);
-    }
+    for (int idx = tid; idx < qn; idx += T) static_cast<F *>(c.tUt)[idx] = F(ut_of(idx / NV, idx % NV));
   } else if (job == 3) {
     // N = M1 Q with Q the smoothness block of the xi1 objective
     for (int idx = tid; idx < n2 * n2; idx += T) {
@@ -388,15 +390,68 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
         for (int k = 0; k < NV; ++k) v += c.M1[I * n2 + bj * NV + k] * GWW[k * NV + j];
       static_cast<F *>(c.tN)[idx] = F(v);
     }
+  } else if (job == 4) {
+    // the fused kernel's lanes, typed constants (an element per thread)
+    F *out = static_cast<F *>(c.lane_t);
+    for (int idx = tid; idx < 4 * lane_t_quads(NV); idx += T) {
+      const int e = idx % 4, lane = idx / 4 % kWave, piece = idx / (4 * kWave);
+      const int I = lane < 4 * NV ? lane % n2 : 0, qb = I / NV, qi = I % NV;
+      double v = 0.0;
+      if (piece < 2 * NP) {
+        const int half = piece / NP, which = piece % NP / (NP / 4), k = 4 * (piece % (NP / 4)) + e;
+        // slot k holds row k xor lane within groups of 4
+        const int r = (k & ~3) | ((k ^ lane) & 3), t = half * hq + lane;
+        if (lane < hq && t < q && r < NV)
+          v = which == 0 ? c.U[t * NV + r] : (which == 1 ? c.V[t * NV + r] : (which == 2 ? c.W[t * NV + r] : ut_of(t, r)));
+      } else if (piece < lane_t_q(NV)) {
+        const int J = 4 * (piece - lane_t_m1(NV)) + e;
+        v = J < n2 ? c.M1[I * n2 + J] : 0.0;
+      } else if (piece < lane_t_m2(NV)) {
+        const int k = 4 * (piece - lane_t_q(NV)) + e;
+        v = k < NV && (qb == 0 || q_cs) ? GWW[qi * NV + k] : 0.0;
+      } else if (piece < lane_t_h2(NV)) {
+        const int k = 4 * (piece - lane_t_m2(NV)) + e;
+        v = k < NV && lane < NV ? c.M2[lane * NV + k] : 0.0;
+      } else {
+        const int k = 4 * (piece - lane_t_h2(NV)) + e;
+        v = k < 6 && lane < NV ? c.H2[lane * 6 + k] : 0.0;
+      }
+      out[idx] = F(v);
+    }
+  } else if (job == 5) {
+    // ... and the FP64 ones
+    for (int idx = tid; idx < 2 * lane_d_pairs(NV); idx += T) {
+      const int e = idx % 2, lane = idx / 2 % kWave, piece = idx / (2 * kWave);
+      const int I = lane < 4 * NV ? lane % n2 : 0, kk = I % NV;
+      double v = 0.0;
+      if (piece < NP) {
+        const int half = piece / (NP / 2), k = 2 * (piece % (NP / 2)) + e, t = half * hq + lane;
+        if (lane < hq && t < q && k < NV) v = c.U[t * NV + k];
+      } else if (piece < lane_d_piece(NV, 0)) {
+        v = c.H1[I * 6 + 2 * (piece - lane_d_h1(NV)) + e];
+      } else {
+        const int which = (piece - lane_d_piece(NV, 0)) / (NP / 2);
+        const int j = 2 * ((piece - lane_d_piece(NV, 0)) % (NP / 2)) + e;
+        if (j < NV) {
+          if (which == LD_Q) v = GWW[kk * NV + j];
+          else if (which == LD_R_ROW) v = c.R[kk * NV + j];
+          else if (which == LD_RINV_COL) v = c.Rinv[j * NV + kk];
+          else if (which == LD_RINV_ROW) v = c.Rinv[kk * NV + j];
+          else if (which == LD_R_COL) v = c.R[j * NV + kk];
+          else v = lane < 12 ? c.Abc[(lane % 6) * NV + j] : 0.0;
+        }
+      }
+      c.lane_d[idx] = v;
+    }
   } else {
     // typed copies
     const double *const src[] = {c.U, c.V, c.W, c.P, c.Pd, c.Pdd, c.M1, c.M2, c.H2};
     void *const dst[] = {c.tU, c.tV, c.tW, c.tP, c.tPd, c.tPdd, c.tM1, c.tM2, c.tH2};
     const int count[] = {qn, qn, qn, qn, qn, qn, n2 * n2, NV * NV, NV * 6};
-    static_assert(sizeof(count) / sizeof(count[0]) == kPackJobs - 4, "a job per copy");
+    static_assert(sizeof(count) / sizeof(count[0]) == kPackJobs - 6, "a job per copy");
 #pragma unroll
-    for (int k = 0; k < kPackJobs - 4; ++k)
-      if (job == 4 + k)
+    for (int k = 0; k < kPackJobs - 6; ++k)
+      if (job == 6 + k)
         for (int i = tid; i < count[k]; i += T) static_cast<F *>(dst[k])[i] = F(src[k][i]);
   }
 }
