@@ -91,7 +91,45 @@ __global__ __launch_bounds__(kWave *kWavesPerBlock) void residual_kernel(ResArgs
     }
     T spsi, cpsi;
     Num<T>::sincos_(psi, &spsi, &cpsi);
-    // obstacles outermost, their positions at t loaded a chunk at a time
+    // f_c of every circle against obstacle j at offset (gx, gy)
+    auto obstacle_residual = [&](T gx, T gy, int j) __attribute__((always_inline)) {
+      const T a = ell[0][j], b = ell[1][j], ab = ell[2][j], a2 = a * a, b2 = b * b;
+#pragma unroll
+      for (int i = 0; i < AM_MAX_CIRCLES; ++i) {
+        if (i >= m) break;
+        const T ri = rr[i];
+        const T px = x + ri * cpsi - gx, py = y + ri * spsi - gy;   // circle centre - obstacle
+        const T xt = slack ? x + ri * c - gx : px, yt = slack ? y + ri * s - gy : py;
+        T fx, fy;
+        if (!literal) {
+          // elliptic angle: (a d cos al, b d sin al) = (xt, yt) max(1, ab/r),
+          // r = |(b xt, a yt)| (eqs. zeta_2, compute_zeta_3); al = 0, d = 1
+          // at the zero vector.  A centre offset whose r^2 is zero or below
+          // the smallest normal number (|offset| ~ 1e-19 m in FP32) counts
+          // as the zero vector: the hardware 1/sqrt is not defined there.
+          const T r2 = b2 * xt * xt + a2 * yt * yt;
+          const T g = fmax(T(1), ab * Num<T>::rsqrt_fast(r2));
+          const bool zero = !(r2 >= kMinNormal<T>);
+          fx = zero ? px - a : px - xt * g;
+          fy = zero ? py : py - yt * g;
+        } else {
+          const T al = atan2z(yt, xt);
+          T sa, ca;
+          Num<T>::sincos_(al, &sa, &ca);
+          const T dd = fmax(T(1), (a * xt * ca + b * yt * sa) / (a * a * ca * ca + b * b * sa * sa));
+          fx = px - a * dd * ca;
+          fy = py - b * dd * sa;
+        }
+        const T f2 = fx * fx + fy * fy;
+        fc2max = fmax(fc2max, f2);
+        fcsq += f2;
+      }
+    };
+    // A circle centre outside an ellipse has f_c = 0 exactly (its angle and
+    // distance reproduce the point), so with headings as x~ and finite values
+    // f_c is formed only for obstacles that some lane's level says are touched.
+    // Obstacles outermost, their positions at t loaded a chunk at a time.
+    const bool all = slack || literal || __ballot(!(isfinite(x) && isfinite(y) && isfinite(cpsi) && isfinite(spsi))) != 0;
     for (int j0 = 0; j0 < n; j0 += kResChunk) {
       T gx[kResChunk], gy[kResChunk];
 #pragma unroll
@@ -104,39 +142,16 @@ __global__ __launch_bounds__(kWave *kWavesPerBlock) void residual_kernel(ResArgs
       for (int u = 0; u < kResChunk; ++u) {
         const int j = j0 + u;
         if (j >= n) break;
-        const T a = ell[0][j], b = ell[1][j], ab = ell[2][j], a2 = a * a, b2 = b * b;
         const T ia2 = ell[3][j], ib2 = ell[4][j];
+        T lv = T(INFINITY);
 #pragma unroll
         for (int i = 0; i < AM_MAX_CIRCLES; ++i) {
           if (i >= m) break;
-          const T ri = rr[i];
-          const T px = x + ri * cpsi - gx[u], py = y + ri * spsi - gy[u];   // circle centre - obstacle
-          const T xt = slack ? x + ri * c - gx[u] : px, yt = slack ? y + ri * s - gy[u] : py;
-          T fx, fy;
-          if (!literal) {
-            // elliptic angle: (a d cos al, b d sin al) = (xt, yt) max(1, ab/r),
-            // r = |(b xt, a yt)| (eqs. zeta_2, compute_zeta_3); al = 0, d = 1
-            // at the zero vector.  A centre offset whose r^2 is zero or below
-            // the smallest normal number (|offset| ~ 1e-19 m in FP32) counts
-            // as the zero vector: the hardware 1/sqrt is not defined there.
-            const T r2 = b2 * xt * xt + a2 * yt * yt;
-            const T g = fmax(T(1), ab * Num<T>::rsqrt_fast(r2));
-            const bool zero = !(r2 >= kMinNormal<T>);
-            fx = zero ? px - a : px - xt * g;
-            fy = zero ? py : py - yt * g;
-          } else {
-            const T al = atan2z(yt, xt);
-            T sa, ca;
-            Num<T>::sincos_(al, &sa, &ca);
-            const T dd = fmax(T(1), (a * xt * ca + b * yt * sa) / (a * a * ca * ca + b * b * sa * sa));
-            fx = px - a * dd * ca;
-            fy = py - b * dd * sa;
-          }
-          const T f2 = fx * fx + fy * fy;
-          fc2max = fmax(fc2max, f2);
-          fcsq += f2;
-          lvl2 = fmin(lvl2, px * px * ia2 + py * py * ib2);
+          const T px = x + rr[i] * cpsi - gx[u], py = y + rr[i] * spsi - gy[u];
+          lv = fmin(lv, px * px * ia2 + py * py * ib2);
         }
+        lvl2 = fmin(lvl2, lv);
+        if (all || __ballot(lv < T(1.001)) != 0) obstacle_residual(gx[u], gy[u], j);
       }
     }
     // velocity and acceleration: the projection onto the disc of radius
