@@ -86,7 +86,7 @@ Desc make_desc(const am_handle *h, const am_problem *p, int32_t batch, int32_t i
   std::memset(&d, 0, sizeof d);
   const Consts &c = h->c;
   d.U = c.tU; d.V = c.tV; d.W = c.tW; d.M1 = c.tM1; d.M2 = c.tM2; d.H2 = c.tH2;
-  d.N = c.tN; d.lane_t = c.lane_t; d.lane_d = c.lane_d; d.R = c.R; d.Rinv = c.Rinv; d.Ud = c.U; d.Abc = c.Abc; d.H1d = c.H1;
+  d.N = c.tN; d.lane_t = c.lane_t; d.lane_d = c.lane_d; d.R = c.R; d.Rinv = c.Rinv; d.Ud = c.UT; d.Abc = c.Abc; d.H1d = c.H1;
   d.ox = p->obs_x; d.oy = p->obs_y; d.oa = p->obs_a; d.ob = p->obs_b;
   d.cx = st->cx; d.cc = st->cc; d.cy = st->cy; d.cs = st->cs; d.cpsi = st->cpsi;
   d.lam = st->lam; d.lampsi = st->lam_psi;
@@ -220,14 +220,14 @@ int am_setup(const am_shape *s, am_handle **out) {
   Consts &c = h->c;
   const size_t qn = size_t(q * nv), es = h->f64 ? 8 : 4;
   const struct { double **p; size_t count; } dparts[] = {
-      {&c.P, qn}, {&c.Pd, qn}, {&c.Pdd, qn}, {&c.U, qn}, {&c.V, qn}, {&c.W, qn},
+      {&c.P, qn}, {&c.Pd, qn}, {&c.Pdd, qn}, {&c.U, qn}, {&c.V, qn}, {&c.W, qn}, {&c.UT, qn},
       {&c.R, size_t(nv * nv)}, {&c.Rinv, size_t(nv * nv)}, {&c.G, size_t(3 * nv * nv)},
       {&c.K1, size_t(N1 * N1)}, {&c.K2, size_t(N2 * N2)}, {&c.M1, size_t(n2 * n2)}, {&c.H1, size_t(n2 * 6)},
       {&c.M2, size_t(nv * nv)}, {&c.H2, size_t(nv * 6)}, {&c.Abc, size_t(6 * nv)},
       {&c.K1b_inv, size_t(N1 * N1)}, {&c.K2b_inv, size_t(N2 * N2)}, {&c.status, 8},
       {&c.lane_d, size_t(2 * amk::lane_d_pairs(nv))}};
   const struct { void **p; size_t count; } tparts[] = {
-      {&c.tU, qn}, {&c.tV, qn}, {&c.tW, qn}, {&c.tP, qn}, {&c.tPd, qn}, {&c.tPdd, qn}, {&c.tUt, qn},
+      {&c.tU, qn}, {&c.tV, qn}, {&c.tW, qn}, {&c.tP, qn}, {&c.tPd, qn}, {&c.tPdd, qn},
       {&c.tM1, size_t(n2 * n2)}, {&c.tM2, size_t(nv * nv)}, {&c.tH2, size_t(nv * 6)}, {&c.tN, size_t(n2 * n2)},
       {&c.lane_t, size_t(4 * amk::lane_t_quads(nv))}};
   size_t bytes = 0;

@@ -23,12 +23,12 @@ constexpr int kDefaultWaves = 2;
 // reinterprets them.
 struct Desc {
   // constants built by the setup kernel (orthonormal basis, KKT inverses)
-  const void *U, *V, *W;     // [q][nv]: x = U z, xdot = V z, xddot = W z
-  const void *M1;            // xi1: [2nv][2nv]
+  const void *U, *V, *W;     // [nv][q]: x = U z, xdot = V z, xddot = W z
+  const void *M1;            // xi1: [2nv][2nv], transposed (output row fastest)
   const void *M2, *H2;       // xi2: [nv][nv] and [nv][6]
-  const void *N;             // [2nv][2nv] M1 Q (Q: smoothness cost of one axis in the z basis)
+  const void *N;             // [2nv][2nv] M1 Q, transposed (Q: smoothness cost of one axis in the z basis)
   const double *R, *Rinv;    // z = R c (Bernstein c), [nv][nv]
-  const double *Ud;          // [q][nv] U in FP64 (positions)
+  const double *Ud;          // [nv][q] U in FP64 (positions)
   const double *Abc;         // [6][nv] boundary rows U, V, W at t = 0 and t = q-1 (z basis)
   const double *H1d;         // [2nv][6] H1 in FP64
   const void *lane_t;        // the fused kernel's lanes' constants, T (see lane_t_half)
@@ -62,7 +62,8 @@ struct Consts {
   double *status;                // [0]: 0 ok, 1 singular xi1 KKT, 2 singular xi2 KKT
   void *tU, *tV, *tW, *tM1, *tM2, *tH2;   // typed copies
   void *tP, *tPd, *tPdd;
-  void *tUt, *tN;                // U M2^T and M1 Q, typed
+  void *tN;                      // M1 Q, typed
+  double *UT;                    // [nv][q] U, time fastest
   void *lane_t;                  // lanes' constants of the fused kernel, typed
   double *lane_d;                // ... and FP64
 };

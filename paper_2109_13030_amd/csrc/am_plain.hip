@@ -74,16 +74,49 @@ Ptrs<T> ptrs_of(void *ws, const PlainWs &w) {
                  b + w.traj8, b + w.psi3, b + w.psih, b + w.alpha, b + w.d, b + w.va4, b + w.chan, b + w.tot};
 }
 
+// Value of lane ^ 32 or lane ^ 16 added (gfx950 lane swaps: both results hold
+// one of the two halves, or of the two rows of each half, on every lane).
+template <int HALF>
+__device__ __forceinline__ float add_swapped(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r = HALF == 32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false)
+                            : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __builtin_bit_cast(float, uint32_t(r[0])) + __builtin_bit_cast(float, uint32_t(r[1]));
+}
+template <int HALF>
+__device__ __forceinline__ double add_swapped(double v) {
+  return v + __shfl_xor(v, HALF);
+}
+
+// Sum over the 64 lanes on every lane, pairs lane ^ 32, 16, 8, 4, 2, 1 in that
+// order: swaps for the halves and rows, then rotations within a row (a value
+// that no longer depends on lane bit 3 is rotated by 4 as well as exchanged)
+// and quad permutations, without the LDS permutes of a shuffle.
 template <typename T>
 __device__ __forceinline__ T wsum(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = add_swapped<32>(v);
+  v = add_swapped<16>(v);
+  v += dpp_rows<0x128, 0xF>(v, T(0));   // row_ror:8
+  v += dpp_rows<0x124, 0xF>(v, T(0));   // row_ror:4
+  v += dpp_rows<0x4E, 0xF>(v, T(0));    // quad_perm [2, 3, 0, 1]
+  v += dpp_rows<0xB1, 0xF>(v, T(0));    // quad_perm [1, 0, 3, 2]
   return v;
+}
+
+// Value of a lane, the same on every lane.
+__device__ __forceinline__ float from_lane(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ double from_lane(double v, int lane) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane(int(b & 0xffffffffLL), lane);
+  const int hi = __builtin_amdgcn_readlane(int(b >> 32), lane);
+  return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | (static_cast<unsigned int>(lo)));
 }
 
 // ---- entry: Bernstein coefficients -> z = R (c - offset), lambda -> R^-T lambda
 template <typename T, int NV>
-__global__ void k_enter(Desc D, Ptrs<T> w) {
+__global__ __launch_bounds__(kThreads) void k_enter(Desc D, Ptrs<T> w) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= D.B * 5 * NV) return;
   const int l = g / (5 * NV), k = g % (5 * NV), b = k / NV, kk = k % NV;
@@ -110,7 +143,7 @@ __global__ void k_enter(Desc D, Ptrs<T> w) {
 // z' = z - H1 (A z - b) + M1 w - N z, the boundary term on the first update
 // only (afterwards A z = b holds)
 template <typename T, int NV>
-__global__ void k_xi1(Desc D, Ptrs<T> w, int first) {
+__global__ __launch_bounds__(kThreads) void k_xi1(Desc D, Ptrs<T> w, int first) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= D.B * 4 * NV) return;
   const int l = g / (4 * NV), k = g % (4 * NV), b = k / NV, kk = k % NV, axis = b >> 1;
@@ -119,8 +152,9 @@ __global__ void k_xi1(Desc D, Ptrs<T> w, int first) {
   const double *r = w.wd + size_t(l) * 4 * NV + axis * 2 * NV;
   const double *z = w.zd + size_t(l) * 4 * NV + axis * 2 * NV;
   double acc = 0.0;
+#pragma unroll
   for (int J = 0; J < 2 * NV; ++J)
-    acc += double(M1[I * 2 * NV + J]) * r[J] - double(NQ[I * 2 * NV + J]) * z[J];
+    acc += double(M1[J * 2 * NV + I]) * r[J] - double(NQ[J * 2 * NV + I]) * z[J];
   if (first) {
     const double *bb = axis == 0 ? D.bx : D.by;
     const double off = axis == 0 ? D.offx : D.offy;
@@ -138,21 +172,24 @@ __global__ void k_xi1(Desc D, Ptrs<T> w, int first) {
 // ---- trajectories on the grid: absolute positions x, y in FP64 (xyd) and
 // xdot, xddot, c, ydot, yddot, s in T (traj8 channels 1-3, 5-7)
 template <typename T, int NV>
-__global__ void k_eval(Desc D, Ptrs<T> w) {
+__global__ __launch_bounds__(kThreads) void k_eval(Desc D, Ptrs<T> w) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= D.B * D.q) return;
   const int l = g / D.q, t = g % D.q, q = D.q;
-  const T *U = static_cast<const T *>(D.U) + t * NV, *V = static_cast<const T *>(D.V) + t * NV,
-          *W = static_cast<const T *>(D.W) + t * NV;
-  const double *Ud = D.Ud + t * NV;
+  const T *U = static_cast<const T *>(D.U) + t, *V = static_cast<const T *>(D.V) + t,
+          *W = static_cast<const T *>(D.W) + t;
+  const double *Ud = D.Ud + t;
   const T *z = w.z + size_t(l) * 4 * NV;
   const double *zd = w.zd + size_t(l) * 4 * NV;
   T v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   double x = 0.0, y = 0.0;
+#pragma unroll
   for (int k = 0; k < NV; ++k) {
-    x += Ud[k] * zd[k]; y += Ud[k] * zd[2 * NV + k];
-    v[1] += V[k] * z[k]; v[2] += W[k] * z[k]; v[3] += U[k] * z[NV + k];
-    v[5] += V[k] * z[2 * NV + k]; v[6] += W[k] * z[2 * NV + k]; v[7] += U[k] * z[3 * NV + k];
+    const double ud = Ud[k * q];
+    const T u = U[k * q], vv = V[k * q], ww = W[k * q];
+    x += ud * zd[k]; y += ud * zd[2 * NV + k];
+    v[1] += vv * z[k]; v[2] += ww * z[k]; v[3] += u * z[NV + k];
+    v[5] += vv * z[2 * NV + k]; v[6] += ww * z[2 * NV + k]; v[7] += u * z[3 * NV + k];
   }
   w.xyd[size_t(l) * 2 * q + t] = x + D.offx;
   w.xyd[size_t(l) * 2 * q + q + t] = y + D.offy;
@@ -163,13 +200,14 @@ __global__ void k_eval(Desc D, Ptrs<T> w) {
 
 // ---- heading trajectory psi = U z_psi with cos, sin
 template <typename T, int NV>
-__global__ void k_eval_psi(Desc D, Ptrs<T> w) {
+__global__ __launch_bounds__(kThreads) void k_eval_psi(Desc D, Ptrs<T> w) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= D.B * D.q) return;
   const int l = g / D.q, t = g % D.q, q = D.q;
-  const T *U = static_cast<const T *>(D.U) + t * NV;
+  const T *U = static_cast<const T *>(D.U) + t;
   T p = T(0);
-  for (int k = 0; k < NV; ++k) p += U[k] * w.zpsi[size_t(l) * NV + k];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) p += U[k * q] * w.zpsi[size_t(l) * NV + k];
   T s, c;
   Num<T>::sincos_(p, &s, &c);
   T *o = w.psi3 + size_t(l) * 3 * q + t;
@@ -179,9 +217,12 @@ __global__ void k_eval_psi(Desc D, Ptrs<T> w) {
   w.psih[size_t(l) * q + t] = p;
 }
 
-// ---- xi2 (one wavefront per trajectory): psi_hat, heading QP, psi
+// ---- xi2 (one wavefront per trajectory): psi_hat, heading QP, psi.  A lane
+// holds time steps lane and lane + 64 with their rows of U; lane k forms z_psi
+// row k, which the others read from it.
 template <typename T, int NV>
-__global__ void k_xi2(Desc D, Ptrs<T> w) {
+__global__ __launch_bounds__(kThreads) void k_xi2(Desc D, Ptrs<T> w) {
+  static_assert(AM_MAX_Q <= 2 * kWave, "two time steps per lane");
   const int lane = threadIdx.x & 63;
   const int l = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
   if (l >= D.B) return;
@@ -191,32 +232,57 @@ __global__ void k_xi2(Desc D, Ptrs<T> w) {
           *H2 = static_cast<const T *>(D.H2);
   const T *tr = w.traj8 + size_t(l) * 8 * q;
   T *p3 = w.psi3 + size_t(l) * 3 * q, *ph = w.psih + size_t(l) * q;
+  T u[2][NV], in[2][5], m2[NV], h2[6];
+  const int row = lane < NV ? lane : 0;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int t = lane + s * kWave < q ? lane + s * kWave : 0;
+    in[s][0] = tr[3 * q + t]; in[s][1] = tr[7 * q + t];
+    in[s][2] = p3[t]; in[s][3] = p3[q + t]; in[s][4] = p3[2 * q + t];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) u[s][k] = U[k * q + t];
+  }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) m2[k] = M2[row * NV + k];
+#pragma unroll
+  for (int e = 0; e < 6; ++e) h2[e] = H2[row * 6 + e];
+  const T lp = w.lampsi[size_t(l) * NV + row];
   T part[NV];
+#pragma unroll
   for (int k = 0; k < NV; ++k) part[k] = T(0);
-  for (int t = lane; t < q; t += 64) {
-    const T c = tr[3 * q + t], s = tr[7 * q + t], p = p3[t], cp = p3[q + t], sp = p3[2 * q + t];
-    const T h = unwrap ? p + atan2z(s * cp - c * sp, c * cp + s * sp) : atan2z(s, c);
-    ph[t] = h;
-    for (int k = 0; k < NV; ++k) part[k] += U[t * NV + k] * h;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int t = lane + s * kWave;
+    const T c = in[s][0], sn = in[s][1], p = in[s][2], cp = in[s][3], sp = in[s][4];
+    const T h = unwrap ? p + atan2z(sn * cp - c * sp, c * cp + sn * sp) : atan2z(sn, c);
+    if (t < q) {
+      ph[t] = h;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) part[k] += u[s][k] * h;
+    }
   }
-  T rhs[NV];
-  for (int k = 0; k < NV; ++k) rhs[k] = w.lampsi[size_t(l) * NV + k] + T(D.rho) * wsum(part[k]);
+  T acc = T(0);
+#pragma unroll
+  for (int e = 0; e < 6; ++e) acc += h2[e] * T(D.bpsi[e]);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc += m2[k] * (from_lane(lp, k) + T(D.rho) * wsum(part[k]));
+  if (lane < NV) w.zpsi[size_t(l) * NV + lane] = acc;
   T zp[NV];
-  for (int k = 0; k < NV; ++k) {
-    T acc = T(0);
-    for (int e = 0; e < 6; ++e) acc += H2[k * 6 + e] * T(D.bpsi[e]);
-    for (int j = 0; j < NV; ++j) acc += M2[k * NV + j] * rhs[j];
-    zp[k] = acc;
-  }
-  if (lane < NV) w.zpsi[size_t(l) * NV + lane] = zp[lane];
-  for (int t = lane; t < q; t += 64) {
+#pragma unroll
+  for (int k = 0; k < NV; ++k) zp[k] = from_lane(acc, k);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int t = lane + s * kWave;
     T p = T(0);
-    for (int k = 0; k < NV; ++k) p += U[t * NV + k] * zp[k];
-    T s, c;
-    Num<T>::sincos_(p, &s, &c);
-    p3[t] = p;
-    p3[q + t] = c;
-    p3[2 * q + t] = s;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) p += u[s][k] * zp[k];
+    T sn, cs;
+    Num<T>::sincos_(p, &sn, &cs);
+    if (t < q) {
+      p3[t] = p;
+      p3[q + t] = cs;
+      p3[2 * q + t] = sn;
+    }
   }
 }
 
@@ -516,9 +582,10 @@ __global__ __launch_bounds__(kItemThreads) void k_targets(Desc D, Ptrs<T> w) {
 // ---- F^T (F xi - g), multipliers and the next right-hand side (one wave
 // per trajectory).  mode 0: initial right-hand side only.
 template <typename T, int NV>
-__global__ void k_contract(Desc D, Ptrs<T> w, int update) {
+__global__ __launch_bounds__(kThreads) void k_contract(Desc D, Ptrs<T> w, int update) {
   const int lane = threadIdx.x & 63;
-  const int l = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+  // (a scalar: the trajectory's values that all lanes share are scalar loads)
+  const int l = blockIdx.x * (blockDim.x / 64) + __builtin_amdgcn_readfirstlane(int(threadIdx.x / 64));
   if (l >= D.B) return;
   const int q = D.q;
   const T *U = static_cast<const T *>(D.U), *V = static_cast<const T *>(D.V), *W = static_cast<const T *>(D.W);
@@ -527,7 +594,7 @@ __global__ void k_contract(Desc D, Ptrs<T> w, int update) {
   for (int k = 0; k < 5 * NV; ++k) part[k] = T(0);
   for (int t = lane; t < q; t += 64) {
     for (int k = 0; k < NV; ++k) {
-      const T u = U[t * NV + k], v = V[t * NV + k], wv = W[t * NV + k];
+      const T u = U[k * q + t], v = V[k * q + t], wv = W[k * q + t];
       part[k] += v * ch[t] + wv * ch[q + t] + u * ch[2 * q + t];
       part[NV + k] += u * ch[3 * q + t];
       part[2 * NV + k] += v * ch[4 * q + t] + wv * ch[5 * q + t] + u * ch[6 * q + t];
@@ -618,7 +685,7 @@ __global__ __launch_bounds__(256) void k_contract_mfma(Desc D, Ptrs<float> w) {
       const int rr = ln & 15, t0 = ks * 16 + (ln >> 4) * 4;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        bv[u][j] = (i < total && rr < NV && t0 + j < q) ? basis[(t0 + j) * NV + rr] : 0.f;
+        bv[u][j] = (i < total && rr < NV && t0 + j < q) ? basis[rr * q + t0 + j] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kFragPer; ++u) {
@@ -665,7 +732,7 @@ __global__ __launch_bounds__(256) void k_contract_mfma(Desc D, Ptrs<float> w) {
 
 // ---- multipliers and the next xi1 right-hand side from the contraction totals
 template <typename T, int NV>
-__global__ void k_update(Desc D, Ptrs<T> w, int update) {
+__global__ __launch_bounds__(kThreads) void k_update(Desc D, Ptrs<T> w, int update) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= D.B * 5 * NV) return;
   const int l = g / (5 * NV), k = g % (5 * NV);
@@ -682,7 +749,7 @@ __global__ void k_update(Desc D, Ptrs<T> w, int update) {
 
 // ---- exit: back to Bernstein coordinates, optional outputs
 template <typename T, int NV>
-__global__ void k_exit(Desc D, Ptrs<T> w) {
+__global__ __launch_bounds__(kThreads) void k_exit(Desc D, Ptrs<T> w) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g < D.B * 5 * NV) {
     const int l = g / (5 * NV), k = g % (5 * NV), b = k / NV, kk = k % NV;

@@ -42,7 +42,8 @@ constexpr int kResChunk = 4;    // obstacle positions loaded together
 constexpr int kResStats = 10;   // per-wave statistics combined across the pair
 
 template <typename T, int NV>
-__global__ __launch_bounds__(kWave *kWavesPerBlock) void residual_kernel(ResArgs A) {
+__global__ __launch_bounds__(kWave *kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1)))
+void residual_kernel(ResArgs A) {
   // per-obstacle constants of the inflated ellipses: a, b, ab, 1/a^2, 1/b^2
   __shared__ T ell[5][AM_MAX_OBS];
   const Desc &D = A.d;
@@ -58,7 +59,9 @@ __global__ __launch_bounds__(kWave *kWavesPerBlock) void residual_kernel(ResArgs
   }
   __syncthreads();
   // two wavefronts per trajectory, taking alternate time steps
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  // (the wavefront's number as a scalar: its trajectory's coefficients are then
+  // scalar loads)
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
   const int half = wave & 1, slot = wave >> 1;
   const int l = blockIdx.x * kTrajPerResBlock + slot;
   const bool live = l < D.B;
@@ -84,7 +87,7 @@ __global__ __launch_bounds__(kWave *kWavesPerBlock) void residual_kernel(ResArgs
     T x = 0, xd = 0, xdd = 0, y = 0, yd = 0, ydd = 0, c = 0, s = 0, psi = 0, psidd = 0;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const T p = P[t * NV + k], pd = Pd[t * NV + k], pdd = Pdd[t * NV + k];
+      const T p = P[k * q + t], pd = Pd[k * q + t], pdd = Pdd[k * q + t];
       x += p * cx[k]; xd += pd * cx[k]; xdd += pdd * cx[k];
       y += p * cy[k]; yd += pd * cy[k]; ydd += pdd * cy[k];
       c += p * cc[k]; s += p * cs[k]; psi += p * cp[k]; psidd += pdd * cp[k];
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(kWave *kWavesPerBlock) void residual_kernel(ResArgs
       const T vals[9] = {x, xd, xdd, y, yd, ydd, psi, T(0), T(0)};
       T psid = 0;
 #pragma unroll
-      for (int k = 0; k < NV; ++k) psid += Pd[t * NV + k] * cp[k];
+      for (int k = 0; k < NV; ++k) psid += Pd[k * q + t] * cp[k];
       const T ps3[3] = {psi, psid, psidd};
       for (int e = 0; e < 3; ++e) {
         bc = fmax(bc, fabs(vals[e] - T(D.bx[o + e])));

@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
   } else if (job == 1) {
     bernstein_inv(c.K2, c.K2b_inv, N2, NV);
   } else if (job == 2) {
-    for (int idx = tid; idx < qn; idx += T) static_cast<F *>(c.tUt)[idx] = F(ut_of(idx / NV, idx % NV));
+    for (int idx = tid; idx < qn; idx += T) c.UT[idx] = c.U[idx % q * NV + idx / q];
   } else if (job == 3) {
     // N = M1 Q with Q the smoothness block of the xi1 objective
     for (int idx = tid; idx < n2 * n2; idx += T) {
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
       if (bj == 0 || q_cs)
 #pragma unroll
         for (int k = 0; k < NV; ++k) v += c.M1[I * n2 + bj * NV + k] * GWW[k * NV + j];
-      static_cast<F *>(c.tN)[idx] = F(v);
+      static_cast<F *>(c.tN)[J * n2 + I] = F(v);
     }
   } else if (job == 4) {
     // the fused kernel's lanes, typed constants (an element per thread)
@@ -444,15 +444,17 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(SetupArgs a) {
       c.lane_d[idx] = v;
     }
   } else {
-    // typed copies
-    const double *const src[] = {c.U, c.V, c.W, c.P, c.Pd, c.Pdd, c.M1, c.M2, c.H2};
-    void *const dst[] = {c.tU, c.tV, c.tW, c.tP, c.tPd, c.tPdd, c.tM1, c.tM2, c.tH2};
-    const int count[] = {qn, qn, qn, qn, qn, qn, n2 * n2, NV * NV, NV * 6};
-    static_assert(sizeof(count) / sizeof(count[0]) == kPackJobs - 6, "a job per copy");
+    // typed copies, time (or the output row) fastest: consecutive lanes of the
+    // plain and residual kernels read consecutive elements
+    const struct { const double *src; void *dst; int rows, cols; } copy[] = {
+        {c.U, c.tU, q, NV}, {c.V, c.tV, q, NV}, {c.W, c.tW, q, NV}, {c.P, c.tP, q, NV}, {c.Pd, c.tPd, q, NV},
+        {c.Pdd, c.tPdd, q, NV}, {c.M1, c.tM1, n2, n2}, {c.M2, c.tM2, 1, NV * NV}, {c.H2, c.tH2, 1, NV * 6}};
+    static_assert(sizeof(copy) / sizeof(copy[0]) == kPackJobs - 6, "a job per copy");
 #pragma unroll
     for (int k = 0; k < kPackJobs - 6; ++k)
       if (job == 6 + k)
-        for (int i = tid; i < count[k]; i += T) static_cast<F *>(dst[k])[i] = F(src[k][i]);
+        for (int i = tid; i < copy[k].rows * copy[k].cols; i += T)
+          static_cast<F *>(copy[k].dst)[i] = F(copy[k].src[i % copy[k].rows * copy[k].cols + i / copy[k].rows]);
   }
 }
 
