@@ -581,45 +581,60 @@ __global__ __launch_bounds__(kItemThreads) void k_targets(Desc D, Ptrs<T> w) {
 
 // ---- F^T (F xi - g), multipliers and the next right-hand side (one wave
 // per trajectory).  mode 0: initial right-hand side only.
+// A lane holds time steps lane and lane + 64 (channels and basis rows), the
+// output blocks are summed one after another (all 5 nv partial sums at once
+// did not fit the registers in FP64).
 template <typename T, int NV>
 __global__ __launch_bounds__(kThreads) void k_contract(Desc D, Ptrs<T> w, int update) {
+  static_assert(AM_MAX_Q <= 2 * kWave, "two time steps per lane");
   const int lane = threadIdx.x & 63;
-  // (a scalar: the trajectory's values that all lanes share are scalar loads)
+  // (a scalar: the trajectory's addresses are scalars)
   const int l = blockIdx.x * (blockDim.x / 64) + __builtin_amdgcn_readfirstlane(int(threadIdx.x / 64));
   if (l >= D.B) return;
   const int q = D.q;
   const T *U = static_cast<const T *>(D.U), *V = static_cast<const T *>(D.V), *W = static_cast<const T *>(D.W);
-  const T *ch = w.chan + size_t(l) * 9 * q;
-  T part[5 * NV];
-  for (int k = 0; k < 5 * NV; ++k) part[k] = T(0);
-  for (int t = lane; t < q; t += 64) {
+  const T *chan = w.chan + size_t(l) * 9 * q;
+  T ch[2][9], u[2][NV], v[2][NV], wv[2][NV];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const bool use = lane + s * kWave < q;
+    const int t = use ? lane + s * kWave : 0;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+      const T x = chan[c * q + t];
+      ch[s][c] = use ? x : T(0);
+    }
+#pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const T u = U[k * q + t], v = V[k * q + t], wv = W[k * q + t];
-      part[k] += v * ch[t] + wv * ch[q + t] + u * ch[2 * q + t];
-      part[NV + k] += u * ch[3 * q + t];
-      part[2 * NV + k] += v * ch[4 * q + t] + wv * ch[5 * q + t] + u * ch[6 * q + t];
-      part[3 * NV + k] += u * ch[7 * q + t];
-      part[4 * NV + k] += u * ch[8 * q + t];
+      u[s][k] = U[k * q + t];
+      v[s][k] = V[k * q + t];
+      wv[s][k] = W[k * q + t];
     }
   }
-  T tot[5 * NV];
-  for (int k = 0; k < 5 * NV; ++k) tot[k] = wsum(part[k]);
+  T trv = T(0);   // lane b nv + k: row k of output block b
+#pragma unroll
+  for (int b = 0; b < 5; ++b) {
+    const int c = b == 0 ? 0 : (b == 1 ? 3 : (b == 2 ? 4 : (b == 3 ? 7 : 8)));
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      T part = T(0);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (b == 0 || b == 2) part += v[s][k] * ch[s][c] + wv[s][k] * ch[s][c + 1] + u[s][k] * ch[s][c + 2];
+        else part += u[s][k] * ch[s][c];
+      }
+      const T tot = wsum(part);
+      trv = lane == b * NV + k ? tot : trv;
+    }
+  }
   double *lam = w.lamd + size_t(l) * 4 * NV;
   if (lane < 4 * NV) {
-    const int k = lane;
-    T trv = T(0);
-    for (int c = 0; c < 4 * NV; ++c)
-      if (c == k) trv = tot[c];
-    double lv = lam[k];
+    double lv = lam[lane];
     if (update) lv -= D.rho * double(trv);
-    lam[k] = lv;
-    w.wd[size_t(l) * 4 * NV + k] = lv - D.rho * double(trv);
+    lam[lane] = lv;
+    w.wd[size_t(l) * 4 * NV + lane] = lv - D.rho * double(trv);
   } else if (update && lane < 5 * NV) {
-    const int kk = lane - 4 * NV;
-    T tp = T(0);
-    for (int c = 0; c < NV; ++c)
-      if (c == kk) tp = tot[4 * NV + c];
-    w.lampsi[size_t(l) * NV + kk] -= T(D.rho_psi) * tp;
+    w.lampsi[size_t(l) * NV + lane - 4 * NV] -= T(D.rho_psi) * trv;
   }
 }
 
