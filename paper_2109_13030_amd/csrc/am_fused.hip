@@ -369,7 +369,14 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     double ae = 0.0;
 #pragma unroll
     for (int k = 0; k < NV; ++k) ae += abc[k] * vzd[ax * A2 + k];
-    const double be = ax == 0 ? Dsrc.bx[e] : Dsrc.by[e];
+    // (selected from scalars: an indexed read would be a load from the
+    // kernel's arguments in host memory)
+    double be = 0.0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const double bxk = uni(Dsrc.bx[k]), byk = uni(Dsrc.by[k]);
+      be = e == k ? (ax == 0 ? bxk : byk) : be;
+    }
     st[lane] = ae - ((e == 0 || e == 3) ? be - off : be);
   }
   wave_sync();
@@ -986,13 +993,15 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
       head = fabs(dh);
       cost = xdd * xdd + ydd * ydd + psdd * psdd;
       if (t == 0 || t == q - 1) {
-        const int o = t == 0 ? 0 : 3;
         const double vx[3] = {xa, double(xd), double(xdd)}, vy[3] = {ya, double(yd), double(ydd)};
         const double vp[3] = {double(psi), double(psd), double(psdd)};
+#pragma unroll
         for (int e = 0; e < 3; ++e) {
-          bc = fmax(bc, T(fabs(vx[e] - Dsrc.bx[o + e])));
-          bc = fmax(bc, T(fabs(vy[e] - Dsrc.by[o + e])));
-          bc = fmax(bc, T(fabs(vp[e] - Dsrc.bpsi[o + e])));
+          const double b0x = uni(Dsrc.bx[e]), b1x = uni(Dsrc.bx[3 + e]), b0y = uni(Dsrc.by[e]), b1y = uni(Dsrc.by[3 + e]);
+          const double b0p = uni(Dsrc.bpsi[e]), b1p = uni(Dsrc.bpsi[3 + e]);
+          bc = fmax(bc, T(fabs(vx[e] - (t == 0 ? b0x : b1x))));
+          bc = fmax(bc, T(fabs(vy[e] - (t == 0 ? b0y : b1y))));
+          bc = fmax(bc, T(fabs(vp[e] - (t == 0 ? b0p : b1p))));
         }
       }
       bad = !isfinite(xa) || !isfinite(ya) || !isfinite(psi);
