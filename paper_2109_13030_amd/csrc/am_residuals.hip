@@ -132,7 +132,11 @@ void residual_kernel(ResArgs A) {
     // distance reproduce the point), so with headings as x~ and finite values
     // f_c is formed only for obstacles that some lane's level says are touched.
     // Obstacles outermost, their positions at t loaded a chunk at a time.
-    const bool all = slack || literal || __ballot(!(isfinite(x) && isfinite(y) && isfinite(cpsi) && isfinite(spsi))) != 0;
+    // (with the slack offsets as x~ it is the difference of the two offsets
+    // outside, and the form is chosen by their own distance)
+    const bool fine = isfinite(x) && isfinite(y) && isfinite(cpsi) && isfinite(spsi) &&
+                      (!slack || (isfinite(c) && isfinite(s)));
+    const bool all = literal || __ballot(!fine) != 0;
     for (int j0 = 0; j0 < n; j0 += kResChunk) {
       T gx[kResChunk], gy[kResChunk];
 #pragma unroll
@@ -154,7 +158,29 @@ void residual_kernel(ResArgs A) {
           lv = fmin(lv, px * px * ia2 + py * py * ib2);
         }
         lvl2 = fmin(lvl2, lv);
-        if (all || __ballot(lv < T(1.001)) != 0) obstacle_residual(gx[u], gy[u], j);
+        if (!slack || all) {
+          if (all || __ballot(lv < T(1.001)) != 0) obstacle_residual(gx[u], gy[u], j);
+          continue;
+        }
+        const T a2 = ell[0][j] * ell[0][j], b2 = ell[1][j] * ell[1][j], edge = T(1.001) * ell[2][j] * ell[2][j];
+        T top = fc2max, sum = fcsq;
+        bool inside = false;
+#pragma unroll
+        for (int i = 0; i < AM_MAX_CIRCLES; ++i) {
+          if (i >= m) break;
+          const T px = x + rr[i] * cpsi - gx[u], py = y + rr[i] * spsi - gy[u];
+          const T xt = x + rr[i] * c - gx[u], yt = y + rr[i] * s - gy[u];
+          inside |= !(b2 * xt * xt + a2 * yt * yt > edge);
+          const T fx = px - xt, fy = py - yt, f2 = fx * fx + fy * fy;
+          top = fmax(top, f2);
+          sum += f2;
+        }
+        if (__ballot(inside) != 0) {
+          obstacle_residual(gx[u], gy[u], j);
+        } else {
+          fc2max = top;
+          fcsq = sum;
+        }
       }
     }
     // velocity and acceleration: the projection onto the disc of radius

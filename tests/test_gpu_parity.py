@@ -384,6 +384,29 @@ def test_solve_residuals_match_oracle_f64(flags, plain):
     np.testing.assert_allclose(got, ref, atol=1e-7, rtol=1e-6)
 
 
+@pytest.mark.parametrize("K", [0, 1, 15])
+@pytest.mark.parametrize("n", [5, 40])
+def test_slack_residuals_crowded_f64(n, K):
+    """The same statistics with the slack copies in a crowded scene, where the
+    slack offsets lie inside some ellipses and outside others (each form of
+    f_c is taken): fused epilogue and residual kernel against the oracle."""
+    import dataclasses
+    import torch
+    from paper_2109_13030_amd import am
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=72, n_obs=n, circles=4)
+    pb = dict(inputs.make_problem(cfg, 61 + n), flags=oracle.XTILDE_SLACK)
+    init = inputs.make_initial(pb, 5, 62, cfg.sigma)
+    h = am.Handle.for_problem(pb, "f64")
+    p = am.DeviceProblem(pb, "f64")
+    st = am.DeviceState(init, len(pb["r"]), n, pb["q"], "f64", residuals=True)
+    am.solve(h, p, st, K)
+    torch.cuda.synchronize()
+    orc, ost = H.run_oracle(pb, init, K)
+    ref = orc.residuals(ost)
+    np.testing.assert_allclose(st.t["res"].cpu().numpy(), ref, atol=1e-7, rtol=1e-6)
+    np.testing.assert_allclose(am.residuals(h, p, st).cpu().numpy(), ref, atol=1e-7, rtol=1e-6)
+
+
 def test_solve_residuals_full_c2_f32():
     """At the benchmark's size (FP32, B = 1000, K = 100) the statistics of the
     fused kernel's epilogue equal the FP64 residual kernel's on the same
