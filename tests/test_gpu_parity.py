@@ -481,6 +481,32 @@ def test_multi_problem_launch_equals_single_launches():
             assert torch.equal(s.t[k], s1.t[k]), k
 
 
+@pytest.mark.parametrize("count", [1, 2, 63, 64, 65, 130, 700])
+def test_multi_problem_counts_around_a_wavefront(count):
+    """Tables of up to a wavefront's 64 problems and above, with empty
+    problems between: each block finds its own problem (bit-identical to a
+    launch of its own, whose start each problem shares)."""
+    import torch
+    from paper_2109_13030_amd import am
+    pb, init = inputs.workload("c1", batch=5)
+    h = am.Handle.for_problem(pb, "f32")
+    p = am.DeviceProblem(pb, "f32")
+    mk = lambda B: am.DeviceState({k: v[:B] for k, v in init.items()}, len(pb["r"]), len(pb["oa"]), pb["q"], "f32",
+                                  outputs=False)
+    sizes = [(3 * k + k // 7) % 6 for k in range(count)]
+    sizes[0] = max(sizes[0], 1)
+    sts = [mk(B) for B in sizes]
+    ref = mk(5)
+    am.solve(h, p, ref, 2)
+    ws = torch.empty(am.multi_workspace_size(count), dtype=torch.uint8, device="cuda")
+    am.solve_multi([h] * count, [p] * count, sts, 2, ws)
+    torch.cuda.synchronize()
+    for key in ("cx", "cpsi", "lam"):
+        got = torch.cat([s.t[key] for s in sts])
+        want = torch.cat([ref.t[key][:B] for B in sizes])
+        assert torch.equal(got, want), key
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_multi_problem_launch_matches_oracle(dtype):
     """One multi-problem launch over problems of different circle and
