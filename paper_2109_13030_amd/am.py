@@ -221,17 +221,43 @@ class Handle:
         return k1, k2, bs
 
 
+def _packed(arrays, dtype):
+    """The arrays rounded to `dtype` in one host buffer, each part starting at
+    a multiple of 16 bytes; returns (buffer, the parts' offsets)."""
+    np_dt = np.float64 if dtype == _torch().float64 else np.float32
+    step = 16 // np.dtype(np_dt).itemsize
+    at, total = [], 0
+    for a in arrays:
+        at.append(total)
+        total += -(-a.size // step) * step
+    buf = np.empty(total, np_dt)
+    with np.errstate(all="ignore"):   # a value out of range becomes an infinity
+        for a, o in zip(arrays, at):
+            buf[o:o + a.size] = a.reshape(-1)
+    return buf, at
+
+
+def _upload(arrays, dtype, device):
+    """Device tensors of the arrays, parts of one allocation and one copy."""
+    buf, at = _packed(arrays, dtype)
+    t = _torch().as_tensor(buf, device=device)
+    return [t[o:o + a.size].view(a.shape) for a, o in zip(arrays, at)]
+
+
 class DeviceProblem:
     """Obstacle table of one problem in device memory plus the scalar data."""
 
     def __init__(self, pb: dict, dtype: str = "f32", device="cuda"):
-        torch = _torch()
         dt = _dt(dtype)
         n, q = len(pb["oa"]), int(pb["q"])
-        self.ox = torch.as_tensor(np.asarray(pb["ox"], np.float64).reshape(n, q), dtype=dt, device=device).contiguous()
-        self.oy = torch.as_tensor(np.asarray(pb["oy"], np.float64).reshape(n, q), dtype=dt, device=device).contiguous()
-        self.oa = torch.as_tensor(np.asarray(pb["oa"], np.float64), dtype=dt, device=device).contiguous()
-        self.ob = torch.as_tensor(np.asarray(pb["ob"], np.float64), dtype=dt, device=device).contiguous()
+        # one upload: the four arrays are parts of one buffer (four uploads,
+        # each a copy that the host waits for, and those of the coefficients and
+        # of the selection were half of a control period of 200 trajectories:
+        # 380 us, 170 with one copy each)
+        self.ox, self.oy, self.oa, self.ob = _upload([np.asarray(pb["ox"], np.float64).reshape(n, q),
+                                                      np.asarray(pb["oy"], np.float64).reshape(n, q),
+                                                      np.asarray(pb["oa"], np.float64),
+                                                      np.asarray(pb["ob"], np.float64)], dt, device)
         p = Problem()
         p.obs_x, p.obs_y, p.obs_a, p.obs_b = (_ptr(t) if n > 0 else ct.c_void_p(0)
                                               for t in (self.ox, self.oy, self.oa, self.ob))
@@ -260,9 +286,10 @@ class DeviceState:
         src.setdefault("lam", np.zeros((B, 4 * nv)))
         if "lam_psi" not in src:
             src["lam_psi"] = src.get("lampsi", np.zeros((B, nv)))
-        self.t = {}
-        for k in self.KEYS:
-            self.t[k] = torch.as_tensor(np.asarray(src[k], np.float64), dtype=dt, device=device).contiguous()
+        # the coefficients are parts of one buffer, so that a new start is one
+        # upload (load_coefficients)
+        src = [np.asarray(src[k], np.float64) for k in self.KEYS]
+        self.t = dict(zip(self.KEYS, _upload(src, dt, device)))
         self.t["traj"] = torch.zeros((B, 3, q), dtype=dt, device=device) if outputs else None
         self.t["va"] = torch.zeros((B, 4, q), dtype=dt, device=device) if projections else None
         self.t["alpha"] = torch.zeros((B, m * n, q), dtype=dt, device=device) if projections else None
@@ -273,17 +300,43 @@ class DeviceState:
     def c(self) -> State:
         s = State()
         for k in ("cx", "cc", "cy", "cs", "cpsi", "lam", "lam_psi", "alpha", "d", "va", "traj", "res"):
-            setattr(s, k, _ptr(self.t.get(k)))
+            t = self.t.get(k)
+            setattr(s, k, None if t is None else t.data_ptr())
         return s
+
+    def coefficients(self):
+        """The five coefficient arrays as one tensor [5, B, nv] over their
+        memory (cx, cc, cy, cs, cpsi) where they are evenly spaced parts of one
+        allocation, as this class makes them; None otherwise (a caller may put
+        tensors of its own in `t`)."""
+        ts = [self.t[k] for k in self.KEYS[:5]]
+        a, gap = ts[0], ts[1].storage_offset() - ts[0].storage_offset()
+        if a.dtype not in (_torch().float32, _torch().float64) or gap < self.B * self.nv or any(
+                t.shape != (self.B, self.nv) or not t.is_contiguous() or t.dtype != a.dtype or t.device != a.device
+                or t.untyped_storage().data_ptr() != a.untyped_storage().data_ptr()
+                or t.storage_offset() != a.storage_offset() + i * gap for i, t in enumerate(ts)):
+            return None
+        return a.as_strided((5, self.B, self.nv), (gap, self.nv, 1))
 
     def load_coefficients(self, init: dict):
         """Overwrites the coefficients (cx, cc, cy, cs, cpsi; missing ones = 0)
         in place and keeps the multipliers (a warm start)."""
         torch = _torch()
-        for k in ("cx", "cc", "cy", "cs", "cpsi"):
+        src = []
+        for k in self.KEYS[:5]:
             v = init.get(k)
-            src = np.zeros((self.B, self.nv)) if v is None else np.asarray(v, np.float64).reshape(self.B, self.nv)
-            self.t[k].copy_(torch.as_tensor(src, dtype=self.t[k].dtype))
+            src.append(np.zeros((self.B, self.nv)) if v is None
+                       else np.asarray(v, np.float64).reshape(self.B, self.nv))
+        whole = self.coefficients()
+        if whole is not None:
+            buf = np.empty(tuple(whole.shape), np.float64 if whole.dtype == torch.float64 else np.float32)
+            with np.errstate(all="ignore"):
+                for b, v in zip(buf, src):
+                    b[...] = v
+            whole.copy_(torch.from_numpy(buf))
+            return
+        for k, v in zip(self.KEYS[:5], src):
+            self.t[k].copy_(torch.as_tensor(v, dtype=self.t[k].dtype))
 
     def numpy(self) -> dict:
         return {k: (v.detach().cpu().numpy().astype(np.float64) if v is not None else None) for k, v in self.t.items()}
@@ -370,12 +423,44 @@ def select_best(h: Handle, res, fc_tol: float, stream=None):
     """am_select_best on residual rows `res` [B, NRES] (device tensor):
     returns (index, cost, max |f_c|) of the best trajectory (synchronises)."""
     torch = _torch()
-    idx = torch.full((1,), -2, dtype=torch.int32, device=res.device)
-    vals = torch.zeros((2,), dtype=res.dtype, device=res.device)
-    check(lib().am_select_best(h.ptr, int(res.shape[0]), _ptr(res), float(fc_tol), _ptr(idx), _ptr(vals),
-                               _stream_ptr(stream)))
-    v = vals.cpu().numpy()
-    return int(idx.item()), float(v[0]), float(v[1])
+    if stream is not None:
+        with torch.cuda.stream(stream):
+            return select_best(h, res, fc_tol)
+    return _selected(_select_best(h, res, fc_tol, 0).cpu().numpy())
+
+
+def _select_best(h: Handle, res, fc_tol: float, extra: int):
+    """Launches am_select_best; its results, and `extra` elements for the
+    caller, share one buffer, so that one copy reads them (_selected)."""
+    out = _torch().empty((4 + extra,), dtype=res.dtype, device=res.device)
+    at = out.data_ptr()
+    check(lib().am_select_best(h.ptr, int(res.shape[0]), _ptr(res), float(fc_tol), ct.c_void_p(at),
+                               ct.c_void_p(at + 2 * out.element_size()), _stream_ptr(None)))
+    return out
+
+
+def _selected(a):
+    return int(a[:1].view(np.int32)[0]), float(a[2]), float(a[3])
+
+
+def select_coefficients(h: Handle, res, fc_tol: float, st: DeviceState):
+    """select_best and the selected trajectory's coefficients {cx, cc, cy, cs,
+    cpsi} in FP64 (None when every trajectory is non-finite), with one copy
+    to the host where the state's coefficients share an allocation."""
+    torch = _torch()
+    keys, nv = st.KEYS[:5], st.nv
+    whole = st.coefficients()
+    if whole is None or whole.dtype != res.dtype or whole.device != res.device:
+        idx, cost, fc = select_best(h, res, fc_tol)
+        coef = None if idx < 0 else {k: st.t[k][idx].double().cpu().numpy() for k in keys}
+        return idx, cost, fc, coef
+    out = _select_best(h, res, fc_tol, 5 * nv)
+    best = out[:1].view(torch.int32)[:1].clamp(min=0)
+    torch.index_select(whole, 1, best, out=out[4:].view(5, 1, nv))
+    a = out.cpu().numpy()
+    idx, cost, fc = _selected(a)
+    coef = None if idx < 0 else {k: a[4 + i * nv:4 + (i + 1) * nv].astype(np.float64) for i, k in enumerate(keys)}
+    return idx, cost, fc, coef
 
 
 class Server:

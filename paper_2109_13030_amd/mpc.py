@@ -221,10 +221,9 @@ class MPC:
             self.state.load_coefficients(init)   # multipliers stay: warm start
         am.solve(self.h, p, self.state, self.K)
         am.residuals(self.h, p, self.state, out=self.res)
-        idx, cost, fc = am.select_best(self.h, self.res, self.fc_tol)
+        idx, cost, fc, coef = am.select_coefficients(self.h, self.res, self.fc_tol, self.state)
         if idx < 0:
             raise RuntimeError("every trajectory of the batch is non-finite")
-        coef = {k: self.state.t[k][idx].double().cpu().numpy() for k in ("cx", "cc", "cy", "cs", "cpsi")}
         return idx, coef, fc
 
     def plan(self, pb: dict):

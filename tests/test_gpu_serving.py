@@ -278,6 +278,37 @@ def test_select_best_rule_on_planted_rows(am, dtype):
             assert cost == res[want, 7] and fc == res[want, 0]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("batch", [1, 5, 64])
+def test_selected_coefficients(am, batch, dtype):
+    """select_coefficients gives the index of select_best and that row of the
+    state, exactly, where the coefficients share an allocation and where the
+    caller put tensors of its own; None when every trajectory is non-finite."""
+    import torch
+    c = _clients(1)[0]
+    h = am.Handle.for_problem(c["problem"], dtype)
+    rng = np.random.default_rng(8)
+    nv = c["problem"]["nv"]
+    init = {k: rng.normal(size=(batch, nv)) for k in ("cx", "cc", "cy", "cs", "cpsi")}
+    st = am.DeviceState(init, 5, c["n"], c["problem"]["q"], dtype)
+    res = torch.as_tensor(rng.uniform(0.0, 0.2, (batch, am.NRES)), dtype=st.t["cx"].dtype, device="cuda")
+    res[:, 11] = 0
+    for own in (False, True):
+        if own:
+            st.t["cs"] = st.t["cs"].clone()
+        assert (st.coefficients() is None) == own
+        want = am.select_best(h, res, 0.05)
+        idx, cost, fc, coef = am.select_coefficients(h, res, 0.05, st)
+        assert (idx, cost, fc) == want and idx >= 0
+        for k, v in coef.items():
+            assert v.dtype == np.float64
+            np.testing.assert_array_equal(v, st.t[k][idx].double().cpu().numpy())
+        bad = res.clone()
+        bad[:, 11] = 1
+        idx, _, _, coef = am.select_coefficients(h, bad, 0.05, st)
+        assert idx == -1 and coef is None
+
+
 def test_server_reports_the_best_trajectory(am):
     """With select_best the server returns, per request, the trajectory that
     the selection rule picks from the residuals its solve wrote: the same

@@ -97,3 +97,49 @@ def test_server_rejects_bad_config(amlib, bad):
     assert len(L.am_last_error()) > 0
     assert L.am_server_submit(None, None, None) == amlib.AM_ERR_INVALID
     L.am_server_destroy(None)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("batch", [0, 1, 3, 8])
+def test_one_upload_equals_one_per_array(amlib, batch, dtype):
+    """The state's and the problem's arrays as parts of one buffer hold what
+    separate tensors hold (odd batches leave gaps between the parts); new
+    coefficients reach the parts, tensors of the caller's own in their place
+    (same or other memory, other types) and nothing beside them."""
+    import torch
+    from paper_2109_13030_amd import inputs
+    pb, init = inputs.workload("c1", batch=max(batch, 1))
+    init = {k: np.asarray(v)[:batch] for k, v in init.items()}
+    dt = torch.float64 if dtype == "f64" else torch.float32
+    want = lambda v: torch.as_tensor(np.asarray(v, np.float64), dtype=dt)
+    p = amlib.DeviceProblem(pb, dtype, device="cpu")
+    for k in ("ox", "oy", "oa", "ob"):
+        assert torch.equal(getattr(p, k), want(pb[k])) and getattr(p, k).is_contiguous()
+    st = amlib.DeviceState(init, 3, len(pb["oa"]), pb["q"], dtype, device="cpu")
+    for k in ("cx", "cy", "cpsi"):
+        assert torch.equal(st.t[k], want(init[k])) and st.t[k].data_ptr() % 16 == 0 or batch == 0
+    nv = pb["nv"]
+    new = {k: np.arange(batch * nv).reshape(batch, nv) / 7.0 + i for i, k in enumerate(("cx", "cc", "cy", "cpsi"))}
+    new["cx"] = new["cx"] * 1e39   # past the FP32 range: infinities
+
+    def check():
+        for k in st.KEYS[:5]:
+            ref = want(new[k]) if k in new else torch.zeros((batch, nv), dtype=dt)
+            assert torch.equal(st.t[k], ref.to(st.t[k].dtype)), k
+    assert st.coefficients() is not None
+    st.load_coefficients(new)
+    check()
+    # parts of a buffer of the caller's, with values of theirs in the gaps
+    own = torch.full((5, batch * nv + 5), -7.0, dtype=dt)
+    for i, k in enumerate(st.KEYS[:5]):
+        st.t[k] = own[i, :batch * nv].view(batch, nv)
+    st.load_coefficients(new)
+    check()
+    assert torch.equal(own[:, batch * nv:], torch.full((5, 5), -7.0, dtype=dt))
+    # separate tensors, one of them with other strides, one of another order
+    st.t["cc"] = torch.zeros((nv, batch), dtype=dt).t()
+    st.t["cx"], st.t["cy"] = st.t["cy"], st.t["cx"]
+    if batch > 1:
+        assert st.coefficients() is None
+    st.load_coefficients(new)
+    check()
