@@ -278,6 +278,28 @@ def test_select_best_rule_on_planted_rows(am, dtype):
             assert cost == res[want, 7] and fc == res[want, 0]
 
 
+@pytest.mark.parametrize("batch", [2, 63, 65, 1023, 1024, 1025, 4096, 4097, 9000])
+def test_select_best_at_the_edges_of_its_block(am, batch):
+    """The best row in the first, last and a middle place, and twice (the
+    lower index wins), among rows of one class, of the other and unusable."""
+    import torch
+    c = _clients(1)[0]
+    h = am.Handle.for_problem(c["problem"], "f32")
+    rng = np.random.default_rng(batch)
+    for tol, col in ((0.3, 7), (0.05, 0)):   # by cost; none qualifies: by max |f_c|
+        for at in (0, batch - 1, batch // 2):
+            res = np.zeros((batch, am.NRES), np.float32)
+            res[:, 0] = rng.uniform(0.1, 0.2, batch)
+            res[:, 7] = rng.uniform(1.0, 5.0, batch)
+            res[:, 11] = rng.integers(0, 2, batch)
+            for i in (at, batch - 1):
+                res[i, 11], res[i, col] = 0, {7: 0.5, 0: 0.09}[col]
+            want = _best_rule(res, np.float32(tol))
+            assert want == at
+            idx, cost, fc = am.select_best(h, torch.as_tensor(res, device="cuda"), tol)
+            assert (idx, cost, fc) == (at, res[at, 7], res[at, 0])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("batch", [1, 5, 64])
 def test_selected_coefficients(am, batch, dtype):
