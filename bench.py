@@ -56,10 +56,10 @@ def bytes_per_launch(q: int, nv: int, m: int, n: int, B: int, K: int, esize: int
 
 def plain_bytes_per_iter(q: int, nv: int, m: int, n: int, B: int, esize: int = 4) -> float:
     """Algorithmic HBM bytes of one plain iteration: alpha, d written by the
-    projection kernel and read by the target kernel (16 m n q per
-    trajectory), plus the per-t channels (8 trajectory, 3 heading, 4 v/a,
-    9 residual values written and read)."""
-    return float(B) * (16 * m * n * q + 2 * (8 + 3 + 1 + 4 + 9) * q * esize)
+    projection kernel (8 m n q per trajectory), the per-t channels (8
+    trajectory, 3 heading, 9 residual values) written and read and the 4 v/a
+    values written."""
+    return float(B) * (8 * m * n * q + (2 * (8 + 3 + 1 + 9) + 4) * q * esize)
 
 
 # Files the fused kernel is compiled from; counters taken on an older build
@@ -549,14 +549,13 @@ def fixed_cost(workload: str = "c2", solves: int = 35):
 
 def copy_by_size(launches=200):
     """Bandwidth of a plain elementwise copy (half the bytes read, half
-    written) for the byte counts one launch of the plain path's elementwise
-    kernels moves (their algorithmic bytes at c2 and c4), launched back to
-    back like the plain path's kernels: what an elementwise launch of that
-    size reaches on this GPU."""
+    written) for the byte counts one launch of the plain path's projection
+    kernel moves (its algorithmic bytes at c2 and c4), launched back to back
+    like the plain path's kernels: what an elementwise launch of that size
+    reaches on this GPU."""
     import torch
     out = []
-    for label, moved in (("c2 k_targets", 30.0e6), ("c2 k_project", 44.8e6),
-                         ("c4 k_targets", 204.8e6), ("c4 k_project", 347.4e6)):
+    for label, moved in (("c2 k_project", 50.8e6), ("c4 k_project", 371.9e6)):
         n = int(moved / 8)
         x = torch.ones(n, dtype=torch.float32, device="cuda")
         y = torch.empty_like(x)
@@ -608,7 +607,7 @@ def main():
                          "workload's K, with and without residual statistics, and exit")
     ap.add_argument("--copy-sizes", action="store_true",
                     help="run only elementwise copies (y = x * 1) that move as many bytes as one launch of "
-                         "the plain path's projection and target kernels at c2 and c4, and exit")
+                         "the plain path's projection kernel at c2 and c4, and exit")
     args = ap.parse_args()
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus != 1 or world != 1:

@@ -3,10 +3,10 @@
 // state (alpha_ij, d_ij of xi3/xi4, Sec. III-C) and the trajectories held in
 // device memory between launches.  It computes the same iteration as the
 // fused kernel (same basis, same readings) and exists as the reference point
-// for the one-launch form; its projection and target kernels are the
-// bandwidth-bound elementwise part of the method.
+// for the one-launch form; its projection kernel is the bandwidth-bound
+// elementwise part of the method.
 //
-// Per iteration:  xi1 -> evaluate -> xi2 -> project (alpha, d) ->
+// Per iteration:  xi1 -> evaluate -> xi2 -> project (alpha, d) and
 //                 targets/residual channels -> reduce + multipliers.
 //
 // The xi1 step is the update form of the fused kernel,
@@ -286,8 +286,8 @@ __global__ __launch_bounds__(kThreads) void k_xi2(Desc D, Ptrs<T> w) {
   }
 }
 
-// The projection and target kernels work on "items" of a trajectory l: the
-// pairs (i, t) = (k / q, k % q) for k < m q, each looping over the n
+// The projection kernel works on "items" of a trajectory l: the pairs
+// (i, t) = (k / q, k % q) for k < (m + 1) q, each looping over the n
 // obstacles.  The trajectory's values at t are loaded once for n outputs,
 // consecutive lanes touch consecutive t of a row of alpha or d, and a thread
 // keeps several independent row accesses in flight.
@@ -325,22 +325,27 @@ __device__ __forceinline__ void stv(T *p, const Vec<T, V> &x) {
   *reinterpret_cast<Vec<T, V> *>(p) = x;
 }
 
-// ---- xi3/xi4: alpha_ij, d_ij for every (l, i, j, t); items (i, t) with
-// i = m are the velocity/acceleration pairs alpha_v, d_v, alpha_a, d_a.
-// An item covers V consecutive time steps (V = 2 when q is even: aligned
-// 8- or 16-byte loads and stores, and half the wavefronts, so that one round
-// of them fills the GPU).  The items of all trajectories form one flat range
-// over small blocks, so the last blocks of a launch are short.
+// ---- xi3/xi4 and the residual channels of F xi - g, one block per
+// trajectory.  Items (i, t), i < m, project circle i against every obstacle
+// (alpha_ij, d_ij, written out) and sum the deviations of the targets from the
+// circle centre; items (m, t) are the velocity/acceleration pairs alpha_v,
+// d_v, alpha_a, d_a.  The partial sums and the pairs meet in LDS and one
+// thread per t forms the channels.  An item covers V consecutive time steps
+// (V = 2 when q is even: aligned 8- or 16-byte loads and stores).
+// Bound: writing alpha and d (B = 1000, n = 10, FP32: 40 MB).  A second kernel
+// that read d back for the sums took 9.2 us after this one's 15.7; both in one
+// take 17.4 (a solve of 10 iterations: 516 -> 429 us).
 // rows per chunk of loads (fewer for FP64 and for two steps per item)
 template <typename T, int V> constexpr int kProjChunk = (sizeof(T) == 4 ? 8 : 4) / V;
 
 template <typename T, int V, bool LITERAL>
-__global__ __launch_bounds__(kThreads) void k_project(Desc D, Ptrs<T> w) {
+__global__ __launch_bounds__(kItemThreads) void k_project(Desc D, Ptrs<T> w) {
   __shared__ T ell[4][AM_MAX_OBS];  // a_j, b_j (grown by the circle radius), 1/a_j^2, 1/b_j^2
+  __shared__ T part[2][AM_MAX_CIRCLES * AM_MAX_Q];
+  __shared__ T pair[4][AM_MAX_Q];
+  const int l = blockIdx.x;
   const int q = D.q, m = D.m, n = D.n;
   const int qv = q / V;   // items per row; V divides q
-  const int per = (m + 1) * qv;
-  const int g = int(blockIdx.x) * kThreads + int(threadIdx.x);
   const bool slack = D.flags & AM_XTILDE_SLACK;
   for (int j = threadIdx.x; j < n; j += blockDim.x) {
     const T a = static_cast<const T *>(D.oa)[j] + T(D.rc), b = static_cast<const T *>(D.ob)[j] + T(D.rc);
@@ -349,204 +354,130 @@ __global__ __launch_bounds__(kThreads) void k_project(Desc D, Ptrs<T> w) {
     ell[2][j] = T(1) / (a * a);
     ell[3][j] = T(1) / (b * b);
   }
-  __syncthreads();
-  if (g >= D.B * per) return;
-  const int l = g / per, k = g - l * per;
-  const int i = k / qv, t = (k - i * qv) * V;
   const T *tr = w.traj8 + size_t(l) * 8 * q, *p3 = w.psi3 + size_t(l) * 3 * q;
-  if (i < m) {
-    const T ri = T(D.r[i]);
-    const double *xyl = w.xyd + size_t(l) * 2 * q;
-    const Vec<double, V> xv = ldd<V>(xyl + t), yv = ldd<V>(xyl + q + t);
-    const Vec<T, V> uxv = slack ? ldv<T, V>(tr + 3 * q + t) : ldv<T, V>(p3 + q + t);
-    const Vec<T, V> uyv = slack ? ldv<T, V>(tr + 7 * q + t) : ldv<T, V>(p3 + 2 * q + t);
-    T rx[V], ry[V];
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      rx[e] = ri * uxv.v[e];
-      ry[e] = ri * uyv.v[e];
-    }
-    const size_t row0 = (size_t(l) * m + i) * n;
-    T *oal = w.alpha + row0 * q + t, *od = w.d + row0 * q + t;
-    const T *oxt = static_cast<const T *>(D.ox) + t, *oyt = static_cast<const T *>(D.oy) + t;
-    // obstacle positions are loaded a chunk at a time, so one memory
-    // latency covers a chunk of outputs
-    constexpr int CH = kProjChunk<T, V>;
-    for (int j0 = 0; j0 < n; j0 += CH) {
-      Vec<T, V> gx[CH], gy[CH];
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const int j = j0 + u < n ? j0 + u : n - 1;
-        gx[u] = ldv<T, V>(oxt + size_t(j) * q);
-        gy[u] = ldv<T, V>(oyt + size_t(j) * q);
-      }
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const int j = j0 + u;
-        if (j >= n) break;
-        const T a = ell[0][j], b = ell[1][j], ia2 = ell[2][j], ib2 = ell[3][j];
-        Vec<T, V> al, dd;
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-          // offset of the robot centre from the obstacle centre in FP64,
-          // rounded once
-          const T xt = T(xv.v[e] - double(gx[u].v[e])) + rx[e], yt = T(yv.v[e] - double(gy[u].v[e])) + ry[e];
-          if constexpr (!LITERAL) {
-            // elliptic angle: the point (a d cos al, b d sin al) is (xt, yt)
-            // itself, so d = sqrt(xt^2/a^2 + yt^2/b^2) (eq. compute_zeta_3)
-            al.v[e] = atan2z(a * yt, b * xt);
-            dd.v[e] = fmax(T(1), Num<T>::sqrt_fast(xt * xt * ia2 + yt * yt * ib2));
-          } else {
-            al.v[e] = atan2z(yt, xt);
-            T sa, ca;
-            Num<T>::sincos_(al.v[e], &sa, &ca);
-            dd.v[e] = fmax(T(1), (a * xt * ca + b * yt * sa) / (a * a * ca * ca + b * b * sa * sa));
-          }
-        }
-        stv<T, V>(oal + size_t(j) * q, al);
-        stv<T, V>(od + size_t(j) * q, dd);
-      }
-    }
-  } else {
-    T *o = w.va4 + size_t(l) * 4 * q;
-    const Vec<T, V> xdv = ldv<T, V>(tr + q + t), ydv = ldv<T, V>(tr + 5 * q + t);
-    const Vec<T, V> xddv = ldv<T, V>(tr + 2 * q + t), yddv = ldv<T, V>(tr + 6 * q + t);
-    Vec<T, V> av, dv, aa, da;
-    const T ivmax = T(1) / T(D.vmax), iamax = T(1) / T(D.amax);
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const T xd = xdv.v[e], yd = ydv.v[e], xdd = xddv.v[e], ydd = yddv.v[e];
-      // with alpha_v = atan2(ydot, xdot), xdot cos alpha_v + ydot sin alpha_v
-      // is the speed itself, so d_v = min(1, |v| / v_max) (eq. compute_dv
-      // clipped to [0, 1]); likewise d_a
-      av.v[e] = atan2z(yd, xd);
-      aa.v[e] = atan2z(ydd, xdd);
-      dv.v[e] = fmin(T(1), Num<T>::sqrt_(xd * xd + yd * yd) * ivmax);
-      da.v[e] = fmin(T(1), Num<T>::sqrt_(xdd * xdd + ydd * ydd) * iamax);
-    }
-    stv<T, V>(o + t, av);
-    stv<T, V>(o + q + t, dv);
-    stv<T, V>(o + 2 * q + t, aa);
-    stv<T, V>(o + 3 * q + t, da);
-  }
-}
-
-// Projection launch: two time steps per item when q is even.
-template <typename T>
-void project(const Desc &D, const Ptrs<T> &w, hipStream_t st) {
-  const size_t rows = size_t(D.B) * (D.m + 1);
-  const bool lit = D.flags & AM_ALPHA_LITERAL;
-  if (D.q % 2 == 0)
-    hipLaunchKernelGGL((lit ? k_project<T, 2, true> : k_project<T, 2, false>), dim3(blocks_for(rows * (D.q / 2))),
-                       dim3(kThreads), 0, st, D, w);
-  else
-    hipLaunchKernelGGL((lit ? k_project<T, 1, true> : k_project<T, 1, false>), dim3(blocks_for(rows * D.q)),
-                       dim3(kThreads), 0, st, D, w);
-}
-
-// ---- residual channels of F xi - g per (l, t), reading alpha and d.  Item
-// (i, t) sums circle i's deviations over the obstacles; the m partial sums
-// of a t meet in LDS and one thread per t forms the channels.
-template <typename T> constexpr int kTgtChunk = sizeof(T) == 4 ? 8 : 4;  // d_ij loads issued together
-
-
-template <typename T, int V>
-__global__ __launch_bounds__(kItemThreads) void k_targets(Desc D, Ptrs<T> w) {
-  __shared__ T part[2][AM_MAX_CIRCLES * AM_MAX_Q];
-  __shared__ T ell[2][AM_MAX_OBS];
-  const int l = blockIdx.x;
-  const int q = D.q, m = D.m, n = D.n;
-  const bool slack = D.flags & AM_XTILDE_SLACK, literal = D.flags & AM_ALPHA_LITERAL;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    ell[0][j] = static_cast<const T *>(D.oa)[j] + T(D.rc);
-    ell[1][j] = static_cast<const T *>(D.ob)[j] + T(D.rc);
-  }
-  __syncthreads();
-  const T *tr = w.traj8 + size_t(l) * 8 * q, *p3 = w.psi3 + size_t(l) * 3 * q;
-  const T *va = w.va4 + size_t(l) * 4 * q;
-  const T *ox = static_cast<const T *>(D.ox), *oy = static_cast<const T *>(D.oy);
-  // V consecutive time steps per item (V = 2 when q is even: every row
-  // offset is then even, so the pairs are aligned vector loads)
-  const int qv = q / V;
   const double *xyl = w.xyd + size_t(l) * 2 * q;
-  for (int k = threadIdx.x; k < m * qv; k += blockDim.x) {
+  // inputs of the channels at t = threadIdx.x, loaded before the items so
+  // that their latency is not waited for at the end (q <= blockDim.x whenever
+  // the items fit one block; otherwise the channel loop loads them itself)
+  T pre[10];
+  const int t0 = threadIdx.x;
+  auto load_pre = [&](int t) __attribute__((always_inline)) {
+    pre[0] = tr[q + t]; pre[1] = tr[2 * q + t]; pre[2] = tr[3 * q + t]; pre[3] = tr[5 * q + t];
+    pre[4] = tr[6 * q + t]; pre[5] = tr[7 * q + t]; pre[6] = p3[t]; pre[7] = p3[q + t];
+    pre[8] = p3[2 * q + t]; pre[9] = w.psih[size_t(l) * q + t];
+  };
+  if (t0 < q) load_pre(t0);
+  __syncthreads();
+  for (int k = threadIdx.x; k < (m + 1) * qv; k += blockDim.x) {
     const int i = k / qv, t = (k - i * qv) * V;
-    const Vec<T, V> cv = ldv<T, V>(tr + 3 * q + t), sv = ldv<T, V>(tr + 7 * q + t);
-    const Vec<double, V> xv = ldd<V>(xyl + t), yv = ldd<V>(xyl + q + t);
-    const Vec<T, V> uxv = slack ? cv : ldv<T, V>(p3 + q + t), uyv = slack ? sv : ldv<T, V>(p3 + 2 * q + t);
-    const T ri = T(D.r[i]);
-    const size_t base = (size_t(l) * m + i) * n * q + t;
-    const T *al = w.alpha + base, *dd = w.d + base;
-    // circle i: sum over obstacles of the deviation of the target from the
-    // circle centre.  Under the elliptic angle a point with d > 1 lies
-    // outside the ellipse and is its own target (eqs. zeta_2,
-    // compute_zeta_3), so the deviation is exactly zero; the literal angle
-    // has no such fixed points.
-    T sx[V], sy[V];
+    if (i < m) {
+      const T ri = T(D.r[i]);
+      const Vec<double, V> xv = ldd<V>(xyl + t), yv = ldd<V>(xyl + q + t);
+      const Vec<T, V> uxv = slack ? ldv<T, V>(tr + 3 * q + t) : ldv<T, V>(p3 + q + t);
+      const Vec<T, V> uyv = slack ? ldv<T, V>(tr + 7 * q + t) : ldv<T, V>(p3 + 2 * q + t);
+      T rx[V], ry[V], sx[V], sy[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) sx[e] = sy[e] = T(0);
-    const T *oxt = ox + t, *oyt = oy + t;
-    // a chunk of d_ij in one memory latency; colliding rows (d_ij <= 1, a
-    // few percent) then load their angle and obstacle position
-    for (int j0 = 0; j0 < n; j0 += kTgtChunk<T>) {
-      Vec<T, V> dv[kTgtChunk<T>];
-#pragma unroll
-      for (int u = 0; u < kTgtChunk<T>; ++u) {
-        if (j0 + u < n) {
-          dv[u] = ldv<T, V>(dd + size_t(j0 + u) * q);
-        } else {
-#pragma unroll
-          for (int e = 0; e < V; ++e) dv[u].v[e] = T(2);
-        }
+      for (int e = 0; e < V; ++e) {
+        rx[e] = ri * uxv.v[e];
+        ry[e] = ri * uyv.v[e];
+        sx[e] = sy[e] = T(0);
       }
+      const size_t row0 = (size_t(l) * m + i) * n;
+      T *oal = w.alpha + row0 * q + t, *od = w.d + row0 * q + t;
+      const T *oxt = static_cast<const T *>(D.ox) + t, *oyt = static_cast<const T *>(D.oy) + t;
+      // obstacle positions are loaded a chunk at a time, so one memory
+      // latency covers a chunk of outputs
+      constexpr int CH = kProjChunk<T, V>;
+      for (int j0 = 0; j0 < n; j0 += CH) {
+        Vec<T, V> gx[CH], gy[CH];
 #pragma unroll
-      for (int u = 0; u < kTgtChunk<T>; ++u) {
-        const int j = j0 + u;
-        bool hit = literal;
+        for (int u = 0; u < CH; ++u) {
+          const int j = j0 + u < n ? j0 + u : n - 1;
+          gx[u] = ldv<T, V>(oxt + size_t(j) * q);
+          gy[u] = ldv<T, V>(oyt + size_t(j) * q);
+        }
 #pragma unroll
-        for (int e = 0; e < V; ++e) hit |= dv[u].v[e] <= T(1);
-        if (j < n && hit) {
-          const Vec<T, V> av = ldv<T, V>(al + size_t(j) * q), gx = ldv<T, V>(oxt + j * q),
-                          gy = ldv<T, V>(oyt + j * q);
+        for (int u = 0; u < CH; ++u) {
+          const int j = j0 + u;
+          if (j >= n) break;
+          const T a = ell[0][j], b = ell[1][j], ia2 = ell[2][j], ib2 = ell[3][j];
+          Vec<T, V> al, dd;
+          T xt[V], yt[V];
+          bool hit = LITERAL;
 #pragma unroll
           for (int e = 0; e < V; ++e) {
-            if (literal || dv[u].v[e] <= T(1)) {
-              const T xt = T(xv.v[e] - double(gx.v[e])) + ri * uxv.v[e];
-              const T yt = T(yv.v[e] - double(gy.v[e])) + ri * uyv.v[e];
+            // offset of the robot centre from the obstacle centre in FP64,
+            // rounded once
+            xt[e] = T(xv.v[e] - double(gx[u].v[e])) + rx[e];
+            yt[e] = T(yv.v[e] - double(gy[u].v[e])) + ry[e];
+            if constexpr (!LITERAL) {
+              // elliptic angle: the point (a d cos al, b d sin al) is (xt, yt)
+              // itself, so d = sqrt(xt^2/a^2 + yt^2/b^2) (eq. compute_zeta_3)
+              al.v[e] = atan2z(a * yt[e], b * xt[e]);
+              dd.v[e] = fmax(T(1), Num<T>::sqrt_fast(xt[e] * xt[e] * ia2 + yt[e] * yt[e] * ib2));
+            } else {
+              al.v[e] = atan2z(yt[e], xt[e]);
               T sa, ca;
-              Num<T>::sincos_(av.v[e], &sa, &ca);
-              sx[e] += ell[0][j] * dv[u].v[e] * ca - xt;
-              sy[e] += ell[1][j] * dv[u].v[e] * sa - yt;
+              Num<T>::sincos_(al.v[e], &sa, &ca);
+              dd.v[e] = fmax(T(1), (a * xt[e] * ca + b * yt[e] * sa) / (a * a * ca * ca + b * b * sa * sa));
+            }
+            hit |= dd.v[e] <= T(1);
+          }
+          stv<T, V>(oal + size_t(j) * q, al);
+          stv<T, V>(od + size_t(j) * q, dd);
+          // the deviation of the target from the circle centre.  Under the
+          // elliptic angle a point with d > 1 lies outside the ellipse and is
+          // its own target (eqs. zeta_2, compute_zeta_3), so the deviation is
+          // exactly zero; the literal angle has no such fixed points.
+          if (hit) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+              if (LITERAL || dd.v[e] <= T(1)) {
+                T sa, ca;
+                Num<T>::sincos_(al.v[e], &sa, &ca);
+                sx[e] += a * dd.v[e] * ca - xt[e];
+                sy[e] += b * dd.v[e] * sa - yt[e];
+              }
             }
           }
         }
       }
-    }
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-      part[0][i * q + t + e] = sx[e];
-      part[1][i * q + t + e] = sy[e];
+      for (int e = 0; e < V; ++e) {
+        part[0][i * q + t + e] = sx[e];
+        part[1][i * q + t + e] = sy[e];
+      }
+    } else {
+      T *o = w.va4 + size_t(l) * 4 * q;
+      const Vec<T, V> xdv = ldv<T, V>(tr + q + t), ydv = ldv<T, V>(tr + 5 * q + t);
+      const Vec<T, V> xddv = ldv<T, V>(tr + 2 * q + t), yddv = ldv<T, V>(tr + 6 * q + t);
+      Vec<T, V> av, dv, aa, da;
+      const T ivmax = T(1) / T(D.vmax), iamax = T(1) / T(D.amax);
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const T xd = xdv.v[e], yd = ydv.v[e], xdd = xddv.v[e], ydd = yddv.v[e];
+        // with alpha_v = atan2(ydot, xdot), xdot cos alpha_v + ydot sin alpha_v
+        // is the speed itself, so d_v = min(1, |v| / v_max) (eq. compute_dv
+        // clipped to [0, 1]); likewise d_a
+        av.v[e] = atan2z(yd, xd);
+        aa.v[e] = atan2z(ydd, xdd);
+        dv.v[e] = fmin(T(1), Num<T>::sqrt_(xd * xd + yd * yd) * ivmax);
+        da.v[e] = fmin(T(1), Num<T>::sqrt_(xdd * xdd + ydd * ydd) * iamax);
+        pair[0][t + e] = av.v[e];
+        pair[1][t + e] = dv.v[e];
+        pair[2][t + e] = aa.v[e];
+        pair[3][t + e] = da.v[e];
+      }
+      stv<T, V>(o + t, av);
+      stv<T, V>(o + q + t, dv);
+      stv<T, V>(o + 2 * q + t, aa);
+      stv<T, V>(o + 3 * q + t, da);
     }
-  }
-  // inputs of the channels at t = threadIdx.x, loaded before the barrier so
-  // that their latency overlaps the wait (q <= blockDim.x whenever m q fits
-  // one block; otherwise the channel loop below loads them itself)
-  T pre[14];
-  const int t0 = threadIdx.x;
-  if (t0 < q) {
-    pre[0] = tr[q + t0]; pre[1] = tr[2 * q + t0]; pre[2] = tr[3 * q + t0]; pre[3] = tr[5 * q + t0];
-    pre[4] = tr[6 * q + t0]; pre[5] = tr[7 * q + t0]; pre[6] = p3[t0]; pre[7] = p3[q + t0];
-    pre[8] = p3[2 * q + t0]; pre[9] = w.psih[size_t(l) * q + t0];
-    pre[10] = va[t0]; pre[11] = va[2 * q + t0]; pre[12] = va[q + t0]; pre[13] = va[3 * q + t0];
   }
   __syncthreads();
   for (int t = threadIdx.x; t < q; t += blockDim.x) {
-    if (t != t0) {
-      pre[0] = tr[q + t]; pre[1] = tr[2 * q + t]; pre[2] = tr[3 * q + t]; pre[3] = tr[5 * q + t];
-      pre[4] = tr[6 * q + t]; pre[5] = tr[7 * q + t]; pre[6] = p3[t]; pre[7] = p3[q + t];
-      pre[8] = p3[2 * q + t]; pre[9] = w.psih[size_t(l) * q + t];
-      pre[10] = va[t]; pre[11] = va[2 * q + t]; pre[12] = va[q + t]; pre[13] = va[3 * q + t];
-    }
+    if (t != t0) load_pre(t);
+    const T av = pair[0][t], dv = pair[1][t], aa = pair[2][t], da = pair[3][t];
     const T c = pre[2], s = pre[5];
     const T cp = pre[7], sp = pre[8];
     T Dx = 0, Dy = 0, DRx = 0, DRy = 0, s1 = 0, s2 = 0;
@@ -558,25 +489,37 @@ __global__ __launch_bounds__(kItemThreads) void k_targets(Desc D, Ptrs<T> w) {
     s1 *= T(n);
     s2 *= T(n);
     T sv, cv, sa, ca;
-    Num<T>::sincos_(pre[10], &sv, &cv);
-    Num<T>::sincos_(pre[11], &sa, &ca);
+    Num<T>::sincos_(av, &sv, &cv);
+    Num<T>::sincos_(aa, &sa, &ca);
     const T vm = T(D.vmax), am = T(D.amax);
     const T dc = c - cp, ds = s - sp;
     const T k1 = slack ? T(0) : s1, k2 = (slack ? T(0) : s2) + T(1);
     T *ch = w.chan + size_t(l) * 9 * q + t;
     // inside the disc (d_v < 1) the velocity is its own target
-    const bool vin = pre[12] < T(1), ain = pre[13] < T(1);
-    ch[0] = vin ? T(0) : pre[0] - vm * pre[12] * cv;  // xdot - g_v
-    ch[q] = ain ? T(0) : pre[1] - am * pre[13] * ca;  // xddot - g_a
+    const bool vin = dv < T(1), ain = da < T(1);
+    ch[0] = vin ? T(0) : pre[0] - vm * dv * cv;       // xdot - g_v
+    ch[q] = ain ? T(0) : pre[1] - am * da * ca;       // xddot - g_a
     ch[2 * q] = k1 * dc - Dx;                         // sum_ij (x + r_i c - g_ob)
     ch[3 * q] = k2 * dc - DRx;                        // sum_ij r_i (...) + (c - cos psi)
-    ch[4 * q] = vin ? T(0) : pre[3] - vm * pre[12] * sv;
-    ch[5 * q] = ain ? T(0) : pre[4] - am * pre[13] * sa;
+    ch[4 * q] = vin ? T(0) : pre[3] - vm * dv * sv;
+    ch[5 * q] = ain ? T(0) : pre[4] - am * da * sa;
     ch[6 * q] = k1 * ds - Dy;
     ch[7 * q] = k2 * ds - DRy;
     const T psi_sign = (D.flags & AM_LAMPSI_LITERAL) ? T(-1) : T(1);
     ch[8 * q] = psi_sign * (pre[6] - pre[9]);
   }
+}
+
+// Projection launch: two time steps per item when q is even.
+template <typename T>
+void project(const Desc &D, const Ptrs<T> &w, hipStream_t st) {
+  const bool lit = D.flags & AM_ALPHA_LITERAL;
+  if (D.q % 2 == 0)
+    hipLaunchKernelGGL((lit ? k_project<T, 2, true> : k_project<T, 2, false>), dim3(D.B),
+                       dim3(item_threads((D.m + 1) * (D.q / 2))), 0, st, D, w);
+  else
+    hipLaunchKernelGGL((lit ? k_project<T, 1, true> : k_project<T, 1, false>), dim3(D.B),
+                       dim3(item_threads((D.m + 1) * D.q)), 0, st, D, w);
 }
 
 // ---- F^T (F xi - g), multipliers and the next right-hand side (one wave
@@ -833,21 +776,6 @@ void xi1(const Desc &D, Ptrs<T> &w, hipStream_t st, int first) {
   w.zdn = t;
 }
 
-// Four time steps per item once the batch gives every SIMD about four
-// wavefronts of them (fewer, wider loads); two below that, where more
-// wavefronts hide more latency.
-constexpr size_t kWideItems = size_t(256) * 4 * 64 * 4;
-
-template <typename T>
-void targets(const Desc &D, const Ptrs<T> &w, hipStream_t st) {
-  if (D.q % 4 == 0 && sizeof(T) == 4 && size_t(D.B) * D.m * D.q / 4 >= kWideItems)
-    hipLaunchKernelGGL((k_targets<T, 4>), dim3(D.B), dim3(item_threads(D.m * D.q / 4)), 0, st, D, w);
-  else if (D.q % 2 == 0)
-    hipLaunchKernelGGL((k_targets<T, 2>), dim3(D.B), dim3(item_threads(D.m * D.q / 2)), 0, st, D, w);
-  else
-    hipLaunchKernelGGL((k_targets<T, 1>), dim3(D.B), dim3(item_threads(D.m * D.q)), 0, st, D, w);
-}
-
 template <typename T, int NV>
 hipError_t run(const Desc &D, void *ws, hipStream_t st) {
   const PlainWs L = plain_layout(D.B, D.q, NV, D.m, D.n, int(sizeof(double) / sizeof(T)));
@@ -859,15 +787,13 @@ hipError_t run(const Desc &D, void *ws, hipStream_t st) {
   hipLaunchKernelGGL((k_eval<T, NV>), dim3(blocks_for(size_t(B) * q)), dim3(kThreads), 0, st, D, w);
   hipLaunchKernelGGL((k_eval_psi<T, NV>), dim3(blocks_for(size_t(B) * q)), dim3(kThreads), 0, st, D, w);
   project<T>(D, w, st);
-  targets<T>(D, w, st);
   contract<T, NV>(D, w, st, 0);
   for (int it = 0; it < D.K; ++it) {
     xi1<T, NV>(D, w, st, it == 0);
     hipLaunchKernelGGL((k_eval<T, NV>), dim3(blocks_for(size_t(B) * q)), dim3(kThreads), 0, st, D, w);
     hipLaunchKernelGGL((k_xi2<T, NV>), dim3(wave_blocks), dim3(kThreads), 0, st, D, w);
     project<T>(D, w, st);
-    targets<T>(D, w, st);
-    contract<T, NV>(D, w, st, 1);
+      contract<T, NV>(D, w, st, 1);
   }
   const size_t exit_work = std::max(size_t(B) * 5 * NV, size_t(B) * q);
   hipLaunchKernelGGL((k_exit<T, NV>), dim3(blocks_for(exit_work)), dim3(kThreads), 0, st, D, w);

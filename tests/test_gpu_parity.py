@@ -276,6 +276,17 @@ def test_largest_sizes_f32():
     _fp32_gate(pb, init, 10)
 
 
+@pytest.mark.parametrize("m,q", [(1, 12), (1, 64), (3, 128), (7, 128), (8, 128), (4, 103), (8, 127)])
+@pytest.mark.parametrize("flags", [0, oracle.ALPHA_LITERAL])
+def test_plain_projection_blocks_f64(m, q, flags):
+    """The plain projection's block per trajectory: fewer items than threads,
+    exactly its 512 threads, and more (one and two time steps per item)."""
+    import dataclasses
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=q, n_obs=5, circles=m)
+    pb = dict(inputs.make_problem(cfg, 71), flags=flags)
+    _compare_f64(pb, inputs.make_initial(pb, 3, 72, cfg.sigma), 4, plain=True)
+
+
 def test_largest_sizes_plain_f64():
     """The per-sub-step path at the largest sizes (its kernels keep no
     obstacle table in LDS), FP64 against the oracle."""
