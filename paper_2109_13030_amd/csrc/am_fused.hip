@@ -187,10 +187,11 @@ __device__ __forceinline__ T row_dot(const T *op, int I, const T *v) {
 // The body and its lambdas are inlined by force: left to itself the compiler
 // keeps the large ones (8 circles, FP64) as functions, and everything they
 // capture (the circles' sums, the basis rows, the state) then lives in
-// scratch memory, 0.6 to 1.8 KB a lane.  Inlined, FP64 with 3 circles (16
-// trajectories, 50 iterations) takes 204 us against 611, FP64 with 5 circles
-// (501 trajectories, 20 iterations, q = 127) 133 us against 558, FP32 with 8
-// circles (333 trajectories, 40 obstacles, 20 iterations) 173 us against 183.
+// scratch memory, 0.6 to 1.8 KB a lane.  By inlining alone FP64 with 3 circles
+// (16 trajectories, 50 iterations) went from 611 to 204 us, FP64 with 5 (501
+// trajectories, 20 iterations, q = 127) from 558 to 133, FP32 with 8 (333
+// trajectories, 40 obstacles, 20 iterations) from 183 to 173; with the list
+// and set-up steps below and the FP64 square root they take 190, 99 and 141.
 template <typename T, int NV, int C, int RED>
 __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds, const FusedLds &L,
                            int lane, int wave) {
