@@ -199,7 +199,7 @@ def run_gpu(args):
         pvalue = B * K * psteps / pwall
         out["plain"] = {"value": pvalue, "ms_per_step": pwall * 1e3 / psteps,
                         "solve_ms_events": float(np.mean(psolve_ms)),
-                        "launches_per_step": 6 * K + 7,
+                        "launches_per_step": 5 * K + 6,
                         "fused_speedup": value / pvalue,
                         "hbm_bytes_per_iteration": plain_bytes_per_iter(q, nv, m, n, B)}
     out["_final"] = last.numpy()
