@@ -261,6 +261,38 @@ def test_obstacle_counts_against_oracle(n):
         _fp32_gate(pb, init, 12)
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [4, 40])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 1e30])
+def test_obstacles_parked_at_infinity(value, n, dtype):
+    """Obstacles at infinity, far past the FP32 squares' range or with no
+    position leave a solve as obstacles out of reach do: the last one (one
+    coordinate, all time steps) and the one before it (both, the second
+    wavefront's time steps).  Reference: the oracle with them 10 km away, where
+    its own rounding of their terms is about 1e-11 m."""
+    import dataclasses
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], n_obs=n)
+    pb = inputs.make_problem(cfg, 81 + n)
+    init = inputs.make_initial(pb, 5, 82, cfg.sigma)
+
+    def parked(v):
+        ox, oy = pb["ox"].copy(), pb["oy"].copy()
+        ox[-1] = ox[-2, 50:] = oy[-2, 50:] = v
+        return dict(pb, ox=ox, oy=oy)
+    far = parked(1e4)
+    for flags in (0, oracle.XTILDE_SLACK):
+        _, _, st = H.run_gpu(dict(parked(value), flags=flags), init, 10, dtype)
+        out = st.numpy()
+        assert all(np.isfinite(out[k]).all() for k in st.KEYS)
+        if dtype == "f32":
+            _fp32_gate(dict(far, flags=flags), init, 10, out=out)
+            continue
+        orc, ost = H.run_oracle(dict(far, flags=flags), init, 10)
+        epos, epsi = H.traj_errors(far, out, orc, ost)
+        assert epos.max() < 1e-8 and epsi.max() < 1e-8
+        assert np.abs(out["lam"] - ost["lam"]).max() < 1e-5 * (1.0 + np.abs(ost["lam"]).max())
+
+
 def _largest_problem(B):
     import dataclasses
     cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=128, n_obs=64, circles=8)
