@@ -305,14 +305,35 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
       v[4 * k] = x.a; v[4 * k + 1] = x.b; v[4 * k + 2] = x.c; v[4 * k + 3] = x.d;
     }
   };
-  pairs(rrow, lane_d_piece(NV, LD_R_ROW), NP / 2);
-  pairs(ricol, lane_d_piece(NV, LD_RINV_COL), NP / 2);
-  pairs(abc, lane_d_piece(NV, LD_ABC), NP / 2);
-  pairs(h1r, lane_d_h1(NV), 3);
-  pairs(udr, half * (NP / 2), NP / 2);
-  pairs(qdr, lane_d_piece(NV, LD_Q), NP / 2);
-  quads(m2r, lane_t_m2(NV), NP / 4);
-  quads(h2r, lane_t_h2(NV), 2);
+  // (all at once, so that one memory latency covers them; under the
+  // three-wavefront budget each where it is used, as together they are 150
+  // registers: with all of them early a solve of no iterations, 1000
+  // trajectories, took 35 us, 24 with each where it is used)
+  constexpr bool kEarly = RED == kRedRows;
+  auto load_change = [&]() __attribute__((always_inline)) {
+    pairs(rrow, lane_d_piece(NV, LD_R_ROW), NP / 2);
+    pairs(ricol, lane_d_piece(NV, LD_RINV_COL), NP / 2);
+    quads(h2r, lane_t_h2(NV), 2);
+  };
+  auto load_abc = [&]() __attribute__((always_inline)) { pairs(abc, lane_d_piece(NV, LD_ABC), NP / 2); };
+  auto load_h1 = [&]() __attribute__((always_inline)) { pairs(h1r, lane_d_h1(NV), 3); };
+  auto load_ud = [&]() __attribute__((always_inline)) { pairs(udr, half * (NP / 2), NP / 2); };
+  auto load_q = [&]() __attribute__((always_inline)) { pairs(qdr, lane_d_piece(NV, LD_Q), NP / 2); };
+  auto load_m2 = [&]() __attribute__((always_inline)) { quads(m2r, lane_t_m2(NV), NP / 4); };
+  auto late = [&](auto load) __attribute__((always_inline)) {
+    if constexpr (!kEarly) {
+      asm volatile("" ::: "memory");   // (not to be moved up)
+      load();
+    }
+  };
+  if constexpr (kEarly) {
+    load_change();
+    load_abc();
+    load_h1();
+    load_ud();
+    load_q();
+    load_m2();
+  }
 
   // lane I of the position block: its coefficient, multiplier and the
   // boundary correction of the first update, in FP64
@@ -330,6 +351,7 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     st[9 * NP + lane] = lp0;
   }
   wave_sync();
+  late(load_change);
   // z = R c and lambda_z = R^-T lambda (unused terms selected away, so that
   // the loops have no lane-dependent bounds)
   auto basis_change = [&](int row, double &z, double &lz) {
@@ -360,6 +382,7 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     vaux[lane] = lampsi0;
   }
   wave_sync();
+  late(load_abc);
   // A z - b of the given coefficients (centred positions), a row per lane,
   // then H1 (A z - b)
   if (lane < 12) {
@@ -379,10 +402,12 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     st[lane] = ae - ((e == 0 || e == 3) ? be - off : be);
   }
   wave_sync();
+  late(load_h1);
   if (prow) {
 #pragma unroll
     for (int e = 0; e < 6; ++e) bcc += h1r[e] * st[axis * 6 + e];
   }
+  late(load_m2);
   // mu = M2 lambda_psi (heading rows)
   T mu = T(0);
   if (hrow) {
@@ -391,6 +416,7 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   }
   wave_sync();
 
+  late(load_ud);
   // ---- per-lane trajectory values at t: positions (absolute, FP64) and
   // the other channels (T).  The positions are formed from the FP64
   // coefficients once and then carried: x' = x + U dz, the product of the
@@ -567,8 +593,26 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     }
   };
   auto project_near = [&](auto count, uint32_t lo, uint32_t hi) __attribute__((always_inline)) {
-    if (n <= 32) project_list(count, std::false_type(), List{lo, 0});
-    else project_list(count, std::true_type(), List{lo, hi});
+    if constexpr (RED != kRedRows) {
+      // (three-wavefront budget: one register set and lanes that are done
+      // masked off.  The pipelined walk above and the copies of the loop for
+      // a known circle count spill more here: B = 4096, n = 20, K = 20, two
+      // trajectories per block 441 us with them, 413 without)
+#pragma unroll
+      for (int i = 0; i < C; ++i) Sx[i] = Sy[i] = T(0);
+#pragma unroll 1
+      for (int base = 0; base < n; base += 32)
+#pragma unroll 1
+        for (uint32_t left = base ? hi : lo; left; left &= left - 1) {
+          const int j = base + __builtin_ctz(left);
+          project_obstacle(count, std::false_type(), *reinterpret_cast<const Pair<T> *>(oxy_t + __umul24(j, qstep)),
+                           opq[j * 2]);
+        }
+    } else if (n <= 32) {
+      project_list(count, std::false_type(), List{lo, 0});
+    } else {
+      project_list(count, std::true_type(), List{lo, hi});
+    }
   };
 
   // ---- xi3/xi4 projection of every (circle, obstacle, t), velocity and
@@ -613,6 +657,11 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
         const T ext = rmax * Num<T>::sqrt_fast(u2lim) * T(1.000001);
         const T extm = ext + margin;
         near_lo = near_hi = 0;
+        // (rolled: unrolled, its tests of n and its addresses were formed
+        // before the iterations and kept, 62 scalar registers spilled to
+        // vector lanes and read back in every iteration; B = 4096, n = 20:
+        // 310 -> 306 us, under the three-wavefront budget 545 -> 489)
+#pragma unroll 1
         for (int j0 = 0; j0 < n; j0 += kVoteChunk) {
           Pair<T> o[kVoteChunk];
           T am[kVoteChunk];
@@ -648,10 +697,11 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
         }
         // exact circle counts for m = C, C - 1 and C - 2 (robots of 3 to 5
         // circles with C = 5), the tested form otherwise
+        constexpr bool kCounts = RED == kRedRows;
         if (m == C) project_near(std::integral_constant<int, C>(), near_lo, near_hi);
-        else if (C > 1 && m == C - 1)
+        else if (kCounts && C > 1 && m == C - 1)
           project_near(std::integral_constant<int, (C > 1 ? C - 1 : 0)>(), near_lo, near_hi);
-        else if (C > 2 && m == C - 2)
+        else if (kCounts && C > 2 && m == C - 2)
           project_near(std::integral_constant<int, (C > 2 ? C - 2 : 0)>(), near_lo, near_hi);
         else project_near(std::integral_constant<int, 0>(), near_lo, near_hi);
       } else {
@@ -821,6 +871,7 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     }
     return acc0 + acc1;
   };
+  late(load_q);
   // Q z, formed once in FP64 and then carried: Q z' = Q z + Q dz
   double qz = 0.0;
   if (prow && (qb == 0 || !(flags & AM_Q_CS_ZERO))) {
