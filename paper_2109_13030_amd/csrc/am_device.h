@@ -82,7 +82,8 @@ struct Num<double> {
   // the rounding of e and of the last step (about one unit in the last place)
   // is what remains, as for a square root followed by a division at a third
   // of their instructions (501 trajectories, q = 127: 107 -> 95 us a solve).
-  // Zero and subnormal arguments give +inf, as in FP32.
+  // Zero and subnormal arguments and NaN give +inf; +inf gives NaN (0 * inf in
+  // e): callers must tolerate it (making it 0 here costs 2.5 % of a solve).
   static __device__ __forceinline__ double rsqrt_fast(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     const double e = fma(-x * y, y, 1.0);

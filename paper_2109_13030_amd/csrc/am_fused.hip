@@ -772,9 +772,15 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
       sum_circles();
     }
     // velocity / acceleration: part of (xdot, ydot) outside the disc
-    // (a zero or subnormal speed gives 1/sqrt = +inf and a factor of 0)
-    const T fv = fmax(T(0), T(1) - vmax * Num<T>::rsqrt_fast(xd * xd + yd * yd));
-    const T fa = fmax(T(0), T(1) - amax * Num<T>::rsqrt_fast(xdd * xdd + ydd * ydd));
+    // (a zero or subnormal speed gives 1/sqrt = +inf and a factor of 0; one
+    // whose square overflows gives 0, in FP64 NaN that fmax makes 0, and a
+    // factor of 1)
+    auto share = [](T bound, T v2) {
+      const T s = bound * Num<T>::rsqrt_fast(v2);
+      return fmax(T(0), T(1) - (sizeof(T) == 8 ? fmax(T(0), s) : s));
+    };
+    const T fv = share(vmax, xd * xd + yd * yd);
+    const T fa = share(amax, xdd * xdd + ydd * ydd);
     const T rvx = xd * fv, rvy = yd * fv, rax = xdd * fa, ray = ydd * fa;
     const T dc = cc - cps, ds = ss - sps;
     const T k1 = slack ? T(0) : s1, k2 = (slack ? T(0) : s2) + T(1);

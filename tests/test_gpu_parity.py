@@ -293,6 +293,26 @@ def test_obstacles_parked_at_infinity(value, n, dtype):
         assert np.abs(out["lam"] - ost["lam"]).max() < 1e-5 * (1.0 + np.abs(ost["lam"]).max())
 
 
+@pytest.mark.parametrize("nv", [8, 11])
+def test_speeds_whose_squares_overflow_f64(nv):
+    """Samples of 1e160 m: the squared speeds and accelerations are infinite
+    and their projections take the whole value off, so that one step brings
+    the coefficients back to the boundary conditions' size up to rounding
+    (2^-53 of the start times the step's amplification, below 1e4)."""
+    import dataclasses
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], n_obs=0, circles=2, nv=nv)
+    pb = inputs.make_problem(cfg, 91)
+    init = inputs.make_initial(pb, 3, 92, cfg.sigma)
+    for k in ("cx", "cy"):
+        init[k] = init[k] * 1e160
+    _, ost = H.run_oracle(pb, init, 1)
+    assert np.abs(ost["cx"]).max() < 1e160 * 1e-10 and np.abs(ost["cy"]).max() < 1e160 * 1e-10
+    _, _, st = H.run_gpu(pb, init, 1, "f64")
+    out = st.numpy()
+    for k in ("cx", "cy"):
+        assert np.abs(out[k]).max() < 1e160 * 1e-10, k
+
+
 def _largest_problem(B):
     import dataclasses
     cfg = dataclasses.replace(inputs.CONFIGS["c2"], q=128, n_obs=64, circles=8)
