@@ -1005,11 +1005,12 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
     };
     // A circle centre outside an ellipse has f_c = 0 exactly (its angle and
     // distance reproduce the point), so with headings as x~ (and finite values
-    // throughout) only this lane's near obstacles can contribute to f_c.  The
-    // least level is then theirs too, or that of an obstacle whose centre is
-    // nearer than the circles' reach plus its larger semi-axis times the least
-    // level found so far; the others are passed over (B = 4096, n = 20: 49 ->
-    // 23 us of a solve).
+    // throughout) only this lane's near obstacles can contribute to f_c, and
+    // those that are not at a finite place.  The least level is then the near
+    // ones' too, or that of an obstacle whose centre is nearer than the
+    // circles' reach plus its larger semi-axis times the least level found so
+    // far; the others are passed over (B = 4096, n = 20: 49 -> 23 us of a
+    // solve).
     const bool fine = !tv || (isfinite(xa) && isfinite(ya) && isfinite(cps) && isfinite(sps) &&
                               (!slack || (isfinite(cc) && isfinite(ss))));
     if (literal_alpha || __ballot(!fine) != 0) {
@@ -1045,38 +1046,46 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
         }
       }
     } else if (n > 0) {
-      if (near_any) {
-        for (uint32_t left = near_lo; left; left &= left - 1) {
-          const int j = __builtin_ctz(left);
-          obstacle_residual(oxy[j * q + t], op + j * 8);
-        }
-        for (uint32_t left = near_hi; left; left &= left - 1) {
-          const int j = 32 + __builtin_ctz(left);
-          obstacle_residual(oxy[j * q + t], op + j * 8);
-        }
-      }
       const T x = T(xa), y = T(ya), ext = rmax * Num<T>::sqrt_fast(u2lim) * T(1.000001);
       auto least_level = [&]() {
         const T v = wave_all(lvl2, T(INFINITY), [](T u, T w) { return fmin(u, w); });
         return Num<T>::sqrt_fast(v) * T(1.00001);   // (rounding up)
       };
-      T reach_a = least_level();
-      for (int j = 0; j < n; ++j) {
-        const Pair<T> o = oxy[j * q + tt];
-        const T *e = op + j * 8;
-        const T dx = x - o.x, dy = y - o.y, reach = (ext + e[OP_AMAX] * reach_a) * T(1.00001);
-        const bool near = tv & !(dx * dx + dy * dy >= reach * reach);
-        if (__ballot(near) == 0) continue;
-        const T dxj = off_x(o.x), dyj = off_y(o.y);
-        T lv = lvl2;
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-          if (i >= m) break;
-          const T px = dxj + rr[i] * cps, py = dyj + rr[i] * sps;
-          lv = fmin(lv, px * px * e[OP_IA2] + py * py * e[OP_IB2]);
+      // the near obstacles, then those without a finite distance (their f_c
+      // is not a number and shows in the sum), which the second loop finds
+      uint32_t lo = near_lo, hi = near_hi;
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+        for (; lo; lo &= lo - 1) {
+          const int j = __builtin_ctz(lo);
+          obstacle_residual(oxy[j * q + t], op + j * 8);
         }
-        lvl2 = tv ? lv : lvl2;
-        reach_a = least_level();
+        for (; hi; hi &= hi - 1) {
+          const int j = 32 + __builtin_ctz(hi);
+          obstacle_residual(oxy[j * q + t], op + j * 8);
+        }
+        if (pass == 1) break;
+        T reach_a = least_level();
+        for (int j = 0; j < n; ++j) {
+          const Pair<T> o = oxy[j * q + tt];
+          const T *e = op + j * 8;
+          const T dx = x - o.x, dy = y - o.y, reach = (ext + e[OP_AMAX] * reach_a) * T(1.00001);
+          const T d2 = dx * dx + dy * dy;
+          const bool far = d2 >= reach * reach, finite = d2 <= std::numeric_limits<T>::max();
+          if (__ballot(tv & !(far & finite)) == 0) continue;
+          if (tv & !finite) (j < 32 ? lo : hi) |= 1u << (j & 31);
+          const T dxj = off_x(o.x), dyj = off_y(o.y);
+          T lv = lvl2;
+#pragma unroll
+          for (int i = 0; i < C; ++i) {
+            if (i >= m) break;
+            const T px = dxj + rr[i] * cps, py = dyj + rr[i] * sps;
+            lv = fmin(lv, px * px * e[OP_IA2] + py * py * e[OP_IB2]);
+          }
+          lvl2 = tv ? lv : lvl2;
+          reach_a = least_level();
+        }
+        if (__ballot((lo | hi) != 0) == 0) break;
       }
     }
     if (tv) {

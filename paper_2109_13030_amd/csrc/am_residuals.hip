@@ -9,6 +9,8 @@
 // residual follows from those forms without evaluating the angle.
 #include <hip/hip_runtime.h>
 
+#include <limits>
+
 #include "am_device.h"
 #include "am_internal.h"
 
@@ -130,7 +132,8 @@ void residual_kernel(ResArgs A) {
     };
     // A circle centre outside an ellipse has f_c = 0 exactly (its angle and
     // distance reproduce the point), so with headings as x~ and finite values
-    // f_c is formed only for obstacles that some lane's level says are touched.
+    // f_c is formed only for obstacles that some lane's level says are touched
+    // (or that have none).
     // Obstacles outermost, their positions at t loaded a chunk at a time.
     // (with the slack offsets as x~ it is the difference of the two offsets
     // outside, and the form is chosen by their own distance)
@@ -159,7 +162,10 @@ void residual_kernel(ResArgs A) {
         }
         lvl2 = fmin(lvl2, lv);
         if (!slack || all) {
-          if (all || __ballot(lv < T(1.001)) != 0) obstacle_residual(gx[u], gy[u], j);
+          // (a level that is no finite number: neither is the obstacle's place,
+          // and its f_c shows in the sum)
+          if (all || __ballot(!(lv >= T(1.001) && lv <= std::numeric_limits<T>::max())) != 0)
+            obstacle_residual(gx[u], gy[u], j);
           continue;
         }
         const T a2 = ell[0][j] * ell[0][j], b2 = ell[1][j] * ell[1][j], edge = T(1.001) * ell[2][j] * ell[2][j];

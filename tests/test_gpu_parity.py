@@ -293,6 +293,36 @@ def test_obstacles_parked_at_infinity(value, n, dtype):
         assert np.abs(out["lam"] - ost["lam"]).max() < 1e-5 * (1.0 + np.abs(ost["lam"]).max())
 
 
+@pytest.mark.parametrize("flags", [0, oracle.XTILDE_SLACK])
+@pytest.mark.parametrize("K", [0, 5])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_statistics_with_parked_obstacles(value, K, flags):
+    """The statistics of the fused epilogue and of the residual kernel say
+    that obstacles are not at finite places: the RMS of f_c is not a number
+    and the other columns are the oracle's with them 10 km away (a maximum or
+    minimum passes over what is not a number)."""
+    import dataclasses
+    from paper_2109_13030_amd import am
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], n_obs=35)
+    pb = inputs.make_problem(cfg, 95)
+    init = inputs.make_initial(pb, 5, 96, cfg.sigma)
+
+    def parked(v):
+        ox, oy = pb["ox"].copy(), pb["oy"].copy()
+        ox[3] = oy[3] = ox[-1] = oy[-1] = v
+        return dict(pb, ox=ox, oy=oy, flags=flags)
+    orc, ost = H.run_oracle(parked(1e4), init, K)
+    ref = orc.residuals(ost)
+    h = am.Handle.for_problem(parked(value), "f64")
+    p = am.DeviceProblem(parked(value), "f64")
+    st = am.DeviceState(init, len(pb["r"]), 35, pb["q"], "f64", residuals=True)
+    am.solve(h, p, st, K)
+    rms = am.RES_NAMES.index("fc_rms")
+    for got in (st.t["res"].cpu().numpy(), am.residuals(h, p, st).cpu().numpy()):
+        assert np.isnan(got[:, rms]).all()
+        np.testing.assert_allclose(np.delete(got, rms, 1), np.delete(ref, rms, 1), atol=1e-7, rtol=1e-6)
+
+
 @pytest.mark.parametrize("nv", [8, 11])
 def test_speeds_whose_squares_overflow_f64(nv):
     """Samples of 1e160 m: the squared speeds and accelerations are infinite
