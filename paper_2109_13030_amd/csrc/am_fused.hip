@@ -1046,7 +1046,7 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
         }
       }
     } else if (n > 0) {
-      const T x = T(xa), y = T(ya), ext = rmax * Num<T>::sqrt_fast(u2lim) * T(1.000001);
+      const T ext = rmax * Num<T>::sqrt_fast(u2lim) * T(1.000001);
       auto least_level = [&]() {
         const T v = wave_all(lvl2, T(INFINITY), [](T u, T w) { return fmin(u, w); });
         return Num<T>::sqrt_fast(v) * T(1.00001);   // (rounding up)
@@ -1069,12 +1069,11 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
         for (int j = 0; j < n; ++j) {
           const Pair<T> o = oxy[j * q + tt];
           const T *e = op + j * 8;
-          const T dx = x - o.x, dy = y - o.y, reach = (ext + e[OP_AMAX] * reach_a) * T(1.00001);
-          const T d2 = dx * dx + dy * dy;
+          const T dxj = off_x(o.x), dyj = off_y(o.y), reach = (ext + e[OP_AMAX] * reach_a) * T(1.00001);
+          const T d2 = dxj * dxj + dyj * dyj;
           const bool far = d2 >= reach * reach, finite = d2 <= std::numeric_limits<T>::max();
           if (__ballot(tv & !(far & finite)) == 0) continue;
           if (tv & !finite) (j < 32 ? lo : hi) |= 1u << (j & 31);
-          const T dxj = off_x(o.x), dyj = off_y(o.y);
           T lv = lvl2;
 #pragma unroll
           for (int i = 0; i < C; ++i) {

@@ -323,6 +323,36 @@ def test_statistics_with_parked_obstacles(value, K, flags):
         np.testing.assert_allclose(np.delete(got, rms, 1), np.delete(ref, rms, 1), atol=1e-7, rtol=1e-6)
 
 
+def test_clearance_level_far_from_the_origin_f32():
+    """The clearance level of the fused epilogue 10 km from the origin, where
+    the FP32 grid is 1 mm: one circle passes eight discs at about the same
+    distance (2 m), with positions between the grid's points, so the least of
+    eight levels that differ by less than the grid is to be found.  Offsets are
+    formed in FP64 and rounded once: within 16 roundings of a level of 4."""
+    from paper_2109_13030_amd import am
+    q, nv, n, B, X0 = 100, 11, 8, 64, 10000.0
+    ulp = float(np.spacing(np.float32(X0)))
+    rng = np.random.default_rng(5)
+    pb, _ = inputs.workload("c1", batch=1)
+    P, _, _ = oracle.basis(q, nv, pb["tf"])
+    cx = np.tile(X0 + np.linspace(0.0, 30.0, nv), (B, 1))
+    cy = X0 + ulp * rng.integers(0, 3, (B, nv))
+    z = np.zeros((B, nv))
+    init = dict(cx=cx, cc=z, cy=cy, cs=z, cpsi=z, lam=np.zeros((B, 4 * nv)), lampsi=z)
+    pb = dict(pb, q=q, nv=nv, r=np.zeros(1), oa=np.full(n, 0.25), ob=np.full(n, 0.25), rc=0.25,
+              ox=np.repeat((P @ cx[0])[10:90:10, None], q, 1), oy=np.full((n, q), X0 + 2.0),
+              bx=np.array([X0, 0, 0, X0 + 30.0, 0, 0]), by=np.array([X0, 0, 0, X0, 0, 0]))
+    pb32, init32 = H.as_stored(pb, init, "f32")
+    orc, ost = H.run_oracle(pb32, init32, 0)
+    at = am.RES_NAMES.index("clear_level")
+    ref = orc.residuals(ost)[:, at]
+    h = am.Handle.for_problem(pb, "f32")
+    st = am.DeviceState(init, 1, n, q, "f32", residuals=True)
+    am.solve(h, am.DeviceProblem(pb, "f32"), st, 0)
+    got = st.t["res"].double().cpu().numpy()[:, at]
+    assert np.abs(got - ref).max() < 16 * 4 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("nv", [8, 11])
 def test_speeds_whose_squares_overflow_f64(nv):
     """Samples of 1e160 m: the squared speeds and accelerations are infinite
