@@ -450,7 +450,10 @@ def select_coefficients(h: Handle, res, fc_tol: float, st: DeviceState):
     torch = _torch()
     keys, nv = st.KEYS[:5], st.nv
     whole = st.coefficients()
-    if whole is None or whole.dtype != res.dtype or whole.device != res.device:
+    # (the gather below runs on the device, where an index past the state is
+    # no error: none is made of an empty state or of more rows than it has)
+    if (whole is None or whole.dtype != res.dtype or whole.device != res.device
+            or st.B == 0 or int(res.shape[0]) > st.B):
         idx, cost, fc = select_best(h, res, fc_tol)
         coef = None if idx < 0 else {k: st.t[k][idx].double().cpu().numpy() for k in keys}
         return idx, cost, fc, coef

@@ -414,3 +414,15 @@ def test_inputs_beyond_the_pinned_arena(am):
     ref = ds.t["traj"].cpu().numpy()
     for i, tr in outs.items():
         np.testing.assert_array_equal(tr, ref, err_msg=f"request {i}")
+
+
+def test_empty_batch_selects_nothing(am):
+    """A control period without samples: no trajectory, no gather from the
+    empty state."""
+    import torch
+    c = _clients(1)[0]
+    h = am.Handle.for_problem(c["problem"], "f32")
+    z = np.zeros((0, c["problem"]["nv"]))
+    st = am.DeviceState(dict(cx=z, cy=z, cpsi=z), 5, c["n"], c["problem"]["q"], "f32")
+    idx, _, _, coef = am.select_coefficients(h, torch.empty((0, am.NRES), device="cuda"), 0.05, st)
+    assert idx == -1 and coef is None

@@ -143,3 +143,43 @@ def test_one_upload_equals_one_per_array(amlib, batch, dtype):
         assert st.coefficients() is None
     st.load_coefficients(new)
     check()
+
+
+@pytest.mark.parametrize("batch,rows,index", [(0, 0, -1), (5, 5, 4), (5, 8, 6), (5, 5, -1), (8, 5, 4)])
+def test_selected_coefficients_stay_in_the_state(amlib, monkeypatch, batch, rows, index):
+    """The selected row is only read where the state has it: with an empty
+    batch there is none, and with more residual rows than trajectories the
+    index may lie past the state (an IndexError, from no device-side
+    gather)."""
+    import torch
+    from paper_2109_13030_amd import inputs
+    pb, init = inputs.workload("c1", batch=max(batch, 1))
+    init = {k: np.asarray(v)[:batch] for k, v in init.items()}
+    st = amlib.DeviceState(init, 3, len(pb["oa"]), pb["q"], "f32", device="cpu")
+    res = torch.zeros((rows, amlib.NRES))
+    gathers = []
+    plain_gather = torch.index_select
+
+    def selected(h, r, tol, extra):
+        out = torch.zeros(4 + extra)
+        out[:1].view(torch.int32)[0] = index
+        return out
+
+    def gather(src, dim, idx, **kw):
+        gathers.append((src.shape[dim], int(idx.max())))
+        assert int(idx.max()) < src.shape[dim], "gather past the state"
+        return plain_gather(src, dim, idx, **kw)
+    monkeypatch.setattr(amlib, "_select_best", selected)
+    monkeypatch.setattr(torch, "index_select", gather)
+    if index >= batch:
+        with pytest.raises(IndexError):
+            amlib.select_coefficients(None, res, 0.05, st)
+        assert not gathers
+        return
+    got, cost, fc, coef = amlib.select_coefficients(None, res, 0.05, st)
+    assert got == index
+    if index < 0:
+        assert coef is None
+    else:
+        for k in st.KEYS[:5]:
+            np.testing.assert_array_equal(coef[k], st.t[k][index].double().numpy())
