@@ -424,6 +424,9 @@ def select_best(h: Handle, res, fc_tol: float, stream=None):
     returns (index, cost, max |f_c|) of the best trajectory (synchronises)."""
     torch = _torch()
     if stream is not None:
+        if not isinstance(stream, torch.cuda.Stream):   # anything with a cuda_stream, as the solves take
+            at = int(stream.cuda_stream)
+            stream = torch.cuda.ExternalStream(at, res.device) if at else torch.cuda.default_stream(res.device)
         with torch.cuda.stream(stream):
             return select_best(h, res, fc_tol)
     return _selected(_select_best(h, res, fc_tol, 0).cpu().numpy())

@@ -426,3 +426,18 @@ def test_empty_batch_selects_nothing(am):
     st = am.DeviceState(dict(cx=z, cy=z, cpsi=z), 5, c["n"], c["problem"]["q"], "f32")
     idx, _, _, coef = am.select_coefficients(h, torch.empty((0, am.NRES), device="cuda"), 0.05, st)
     assert idx == -1 and coef is None
+
+
+def test_select_best_takes_any_stream_handle(am):
+    """A stream given as an object with a cuda_stream (as the solves take it),
+    of a side stream and of the default one."""
+    import types
+    import torch
+    c = _clients(1)[0]
+    h = am.Handle.for_problem(c["problem"], "f32")
+    res = torch.zeros((9, am.NRES), device="cuda")
+    res[:, 7] = torch.arange(9, 0, -1, device="cuda")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for s in (side, types.SimpleNamespace(cuda_stream=side.cuda_stream), types.SimpleNamespace(cuda_stream=0)):
+        assert am.select_best(h, res, 0.05, stream=s) == (8, 1.0, 0.0)
