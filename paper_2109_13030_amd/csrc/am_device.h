@@ -202,7 +202,9 @@ __host__ __device__ constexpr int lane_d_pairs(int nv) { return lane_d_piece(nv,
 
 // LDS carve-up of the fused kernel, in elements of T.  Offsets are multiples
 // of 8 elements, so Pair and Quad reads (and FP64 pairs when T is float)
-// are aligned.
+// are aligned.  m1 and qrows are filled and read under the three-wavefront
+// budget only (the other builds hold those rows in registers); they are in
+// every layout, so that the problem sizes a device takes do not depend on it.
 struct FusedLds {
   int oxy;                 // obstacle centres, Pair [n][q]
   int op;                  // per-obstacle parameters [n][8] (OP_*)

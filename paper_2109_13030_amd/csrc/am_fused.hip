@@ -2,8 +2,9 @@
 //
 // Two wavefronts own one trajectory for all K iterations: wave h of the pair
 // holds the time steps t = h*ceil(q/2) + lane.  A block carries `tile`
-// trajectories and shares the LDS copy of the problem's obstacle table and
-// KKT operators.  Everything the iteration carries (multipliers,
+// trajectories and shares the LDS copy of the problem's obstacle table (and,
+// under the three-wavefront budget, of the KKT operators, whose rows each lane
+// otherwise holds in registers).  Everything the iteration carries (multipliers,
 // coefficients, targets) stays in registers and LDS; global memory is read
 // for the initial state and written for the final one only.  Sums over t
 // are formed per wave, exchanged through LDS and added in a fixed order, so
@@ -74,7 +75,8 @@ constexpr int kVoteChunk = 8;   // obstacles whose positions are loaded together
 // [m] slack of the near-obstacle lists, see project_reduce: a wider one renews
 // them less often but holds more obstacles (an iteration at B = 4096, n = 20
 // with 0.12 / 0.25 / 0.4 / 0.6 m: 14.6 / 13.2 / 12.7 / 12.5 us; B = 1000, n =
-// 10: 2.42 / 2.30 / 2.26 / 2.30 us)
+// 10: 2.42 / 2.30 / 2.26 / 2.30 us; 0.45 lies between the two best, of which
+// either is within 2 % in both)
 constexpr double kVoteMargin = 0.45;
 
 // Wave-uniform copies of descriptor fields: the compiler then keeps them in
@@ -1237,9 +1239,9 @@ __device__ __forceinline__ void fused_block(const Desc &D) {
   const FusedLds L = fused_layout(q, n, NV, TILE, RED, int(sizeof(double) / sizeof(T)));
   constexpr int N2 = 2 * NV, A2 = pad4(N2);
 
-  // block-wide: obstacle tables ((x, y) pairs), inflated semi-axes,
-  // operators as Quad [a2/4][2nv], zeroed per-wave areas (their padding
-  // entries are read as zeros)
+  // block-wide: obstacle tables ((x, y) pairs), inflated semi-axes, under the
+  // three-wavefront budget the operators as Quad [a2/4][2nv], zeroed per-wave
+  // areas (their padding entries are read as zeros)
   const T *gox = static_cast<const T *>(D.ox), *goy = static_cast<const T *>(D.oy);
   const T rc = T(D.rc);
   Pair<T> *oxy = reinterpret_cast<Pair<T> *>(lds + L.oxy);

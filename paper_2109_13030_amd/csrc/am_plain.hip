@@ -357,16 +357,16 @@ __global__ __launch_bounds__(kItemThreads) void k_project(Desc D, Ptrs<T> w) {
   const T *tr = w.traj8 + size_t(l) * 8 * q, *p3 = w.psi3 + size_t(l) * 3 * q;
   const double *xyl = w.xyd + size_t(l) * 2 * q;
   // inputs of the channels at t = threadIdx.x, loaded before the items so
-  // that their latency is not waited for at the end (q <= blockDim.x whenever
-  // the items fit one block; otherwise the channel loop loads them itself)
-  T pre[10];
+  // that their latency is not waited for at the end (a thread per t: the (m +
+  // 1) q / V items are at least q, as m >= 1 and V <= 2)
+  static_assert(V <= 2 && AM_MAX_Q <= kItemThreads, "a thread per time step");
   const int t0 = threadIdx.x;
-  auto load_pre = [&](int t) __attribute__((always_inline)) {
-    pre[0] = tr[q + t]; pre[1] = tr[2 * q + t]; pre[2] = tr[3 * q + t]; pre[3] = tr[5 * q + t];
-    pre[4] = tr[6 * q + t]; pre[5] = tr[7 * q + t]; pre[6] = p3[t]; pre[7] = p3[q + t];
-    pre[8] = p3[2 * q + t]; pre[9] = w.psih[size_t(l) * q + t];
-  };
-  if (t0 < q) load_pre(t0);
+  T pre[10];
+  if (t0 < q) {
+    pre[0] = tr[q + t0]; pre[1] = tr[2 * q + t0]; pre[2] = tr[3 * q + t0]; pre[3] = tr[5 * q + t0];
+    pre[4] = tr[6 * q + t0]; pre[5] = tr[7 * q + t0]; pre[6] = p3[t0]; pre[7] = p3[q + t0];
+    pre[8] = p3[2 * q + t0]; pre[9] = w.psih[size_t(l) * q + t0];
+  }
   __syncthreads();
   for (int k = threadIdx.x; k < (m + 1) * qv; k += blockDim.x) {
     const int i = k / qv, t = (k - i * qv) * V;
@@ -475,8 +475,8 @@ __global__ __launch_bounds__(kItemThreads) void k_project(Desc D, Ptrs<T> w) {
     }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < q; t += blockDim.x) {
-    if (t != t0) load_pre(t);
+  if (t0 < q) {
+    const int t = t0;
     const T av = pair[0][t], dv = pair[1][t], aa = pair[2][t], da = pair[3][t];
     const T c = pre[2], s = pre[5];
     const T cp = pre[7], sp = pre[8];
@@ -793,7 +793,7 @@ hipError_t run(const Desc &D, void *ws, hipStream_t st) {
     hipLaunchKernelGGL((k_eval<T, NV>), dim3(blocks_for(size_t(B) * q)), dim3(kThreads), 0, st, D, w);
     hipLaunchKernelGGL((k_xi2<T, NV>), dim3(wave_blocks), dim3(kThreads), 0, st, D, w);
     project<T>(D, w, st);
-      contract<T, NV>(D, w, st, 1);
+    contract<T, NV>(D, w, st, 1);
   }
   const size_t exit_work = std::max(size_t(B) * 5 * NV, size_t(B) * q);
   hipLaunchKernelGGL((k_exit<T, NV>), dim3(blocks_for(exit_work)), dim3(kThreads), 0, st, D, w);
