@@ -1348,7 +1348,11 @@ hipError_t launch_tile(const Desc &single, const Desc *table, int nprob, int nbl
   switch (tile) {
     case 1: return launch_t<T, NV, C, 1, WAVES>(single, table, nprob, nblocks, st, lds_bytes);
     case 2: return launch_t<T, NV, C, 2, WAVES>(single, table, nprob, nblocks, st, lds_bytes);
-    case 4: return launch_t<T, NV, C, 4, WAVES>(single, table, nprob, nblocks, st, lds_bytes);
+    case 4:
+      // (FP64 with 11 coefficients needs 166 KB of LDS here without any
+      // obstacle; a CU has 160, so the caller's LDS check refuses it)
+      if constexpr (sizeof(T) == 8 && NV > 8) return hipErrorInvalidValue;
+      else return launch_t<T, NV, C, 4, WAVES>(single, table, nprob, nblocks, st, lds_bytes);
     default: return hipErrorInvalidValue;
   }
 }
