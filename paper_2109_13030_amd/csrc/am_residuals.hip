@@ -9,8 +9,6 @@
 // residual follows from those forms without evaluating the angle.
 #include <hip/hip_runtime.h>
 
-#include <limits>
-
 #include "am_device.h"
 #include "am_internal.h"
 
@@ -162,10 +160,11 @@ void residual_kernel(ResArgs A) {
         }
         lvl2 = fmin(lvl2, lv);
         if (!slack || all) {
-          // (a level that is no finite number: neither is the obstacle's place,
-          // and its f_c shows in the sum)
-          if (all || __ballot(!(lv >= T(1.001) && lv <= std::numeric_limits<T>::max())) != 0)
-            obstacle_residual(gx[u], gy[u], j);
+          // (or a level that is no finite number: neither is the obstacle's
+          // place, and its f_c shows in the sum; one class test for both)
+          // (0x1C0: zero, subnormal or normal, positive)
+          const bool outside = __builtin_isfpclass(lv - T(1.001), 0x1C0);
+          if (all || __ballot(!outside) != 0) obstacle_residual(gx[u], gy[u], j);
           continue;
         }
         const T a2 = ell[0][j] * ell[0][j], b2 = ell[1][j] * ell[1][j], edge = T(1.001) * ell[2][j] * ell[2][j];
