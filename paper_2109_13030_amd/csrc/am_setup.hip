@@ -18,8 +18,8 @@
 // its matrices in global memory (serial pivot searches, one block-wide
 // reduction per Gram-Schmidt coefficient) took 556 us; these take 59 + 13 us
 // (q = 100, nv = 11, set-ups repeated: basis 8, QR 17, elimination 25, Gram
-// matrices 2 us; the second kernel took 70 us as a process's only one, its
-// unrolled jobs, of 368 bytes of scratch a lane, still to be fetched).
+// matrices 2 us; as the only one of a process the second kernel, whose
+// unrolled jobs hold 368 bytes of scratch a lane, took 14 to 70 us).
 #include <hip/hip_runtime.h>
 
 #include "am_device.h"
