@@ -202,14 +202,17 @@ __host__ __device__ constexpr int lane_d_pairs(int nv) { return lane_d_piece(nv,
 
 // LDS carve-up of the fused kernel, in elements of T.  Offsets are multiples
 // of 8 elements, so Pair and Quad reads (and FP64 pairs when T is float)
-// are aligned.  m1 and qrows are filled and read under the three-wavefront
-// budget only (the other builds hold those rows in registers); they are in
-// every layout, so that the problem sizes a device takes do not depend on it.
+// are aligned.  m1 and qrows hold operators under the three-wavefront budget
+// only (the other builds hold those rows in registers); they are in every
+// layout, so that the problem sizes a device takes do not depend on it.  In
+// the others the obstacle tables have a row n there (the idle steps of the
+// near lists): that of the centres at the start of m1, and the parameters
+// start 8 elements into qrows' end.
 struct FusedLds {
-  int oxy;                 // obstacle centres, Pair [n][q]
-  int op;                  // per-obstacle parameters [n][8] (OP_*)
+  int oxy;                 // obstacle centres, Pair [n][q], or [n + 1][q]
   int m1;                  // [2nv][2nv] operator M1 as Quad [a2/4][2nv]
   int qrows;               // rows of Q = blockdiag(W^T W, W^T W or 0) as [2][nv][pad4(nv)]
+  int op;                  // per-obstacle parameters [n][8] (OP_*), or [n + 1][8]
   int xch;                 // [traj][half][kXchHalf] exchange area
   int wave0, wave_stride;  // per-wave areas
   int total;
@@ -253,9 +256,9 @@ __host__ __device__ inline FusedLds fused_layout(int q, int n, int nv, int tile,
   const int a2 = pad4(2 * nv);
   int o = 0;
   L.oxy = o; o += pad8(2 * n * q);
-  L.op = o; o += 8 * n;
   L.m1 = o; o += a2 * 2 * nv;
   L.qrows = o; o += pad8(2 * nv * pad4(nv));
+  L.op = red_rows == kRedRows ? o - 8 : o; o += 8 * n;
   L.xch = o; o += tile * 2 * kXchHalf;
   const WaveLds w = wave_layout(nv, red_rows, dw);
   L.wave_stride = pad8(w.red + red_rows * kRedRowStride);

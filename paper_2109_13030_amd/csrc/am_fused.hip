@@ -92,6 +92,8 @@ __device__ __forceinline__ double uni(double v) {
   return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | (static_cast<unsigned int>(lo)));
 }
 
+__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
 // Value of the neighbouring lane (lane ^ 1) through a DPP quad permutation.
 __device__ __forceinline__ float lane_xor1(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
@@ -532,18 +534,12 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
   // obstacles), not as many as are near some lane (4.7): an obstacle is near
   // for a few seconds of the horizon only (B = 4096, n = 20, K = 20: 396 ->
   // 354 us; B = 1000, n = 10: 84 -> 79 us).  A lane whose list is done reads
-  // an obstacle with a finite centre and ab = 0, which adds exactly zero (fmax
-  // drops the NaN of 0 * inf).  A list has one word for up to 32 obstacles,
-  // two above.
+  // row n of the tables, an obstacle at the origin with ab = 0, which adds
+  // exactly zero (fmax drops the NaN of 0 * inf); one of the problem's would
+  // have to be at a finite place for that, and callers park those they do not
+  // need at infinity.  A list has one word for up to 32 obstacles, two above.
   const int qstep = q * int(sizeof(Pair<T>));
   const char *oxy_t = reinterpret_cast<const char *>(oxy + tt);
-  // the obstacle of such idle steps: the last one whose centre is finite at
-  // every lane's t.  (Callers park obstacles they do not need at infinity;
-  // those are near no lane, and read in an idle step they would add inf * 0.
-  // If every obstacle is at infinity at some lane's t, the solve is NaN.)
-  int jidle = n - 1;
-  auto not_finite = [&](const Pair<T> o) { return __ballot(!(isfinite(o.x) && isfinite(o.y))) != 0; };
-  while (jidle > 0 && not_finite(oxy[jidle * q + tt])) --jidle;
   struct List { uint32_t lo, hi; };
   auto next_near = [&](auto wide, List &list, Pair<T> &o, Quad<T> &p) __attribute__((always_inline)) {
     // lowest set bit, all ones when there is none
@@ -560,10 +556,9 @@ __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, i
       list.hi &= word ? ~0u : list.hi - 1;
     }
     list.lo &= list.lo - 1;
-    const uint32_t j = int(low) < 0 ? uint32_t(jidle) : low;
+    const uint32_t j = umin(low, uint32_t(n));
     o = *reinterpret_cast<const Pair<T> *>(oxy_t + __umul24(j, uint32_t(qstep)));
     p = opq[j * 2];
-    p.c = int(low) < 0 ? T(0) : p.c;
   };
   // keeps the loads of a next obstacle before this point (the compiler would
   // sink them to their first use and wait there)
@@ -1256,6 +1251,12 @@ __device__ __forceinline__ void fused_block(const Desc &D) {
 #pragma unroll
     for (int k = 0; k < kFill; ++k)
       if (i0 + k * BD < n * q) oxy[i0 + k * BD] = v[k];
+  }
+  // (row n, for the idle steps of the near lists)
+  if constexpr (RED == kRedRows) {
+    static_assert(A2 * N2 >= 2 * AM_MAX_Q, "row n lies within m1");
+    for (int i = tid; i < q; i += BD) oxy[n * q + i] = Pair<T>{T(0), T(0)};
+    if (tid < 8) lds[L.op + n * 8 + tid] = tid == OP_A2 || tid == OP_B2 ? T(1) : T(0);
   }
   for (int j = tid; j < n; j += blockDim.x) {
     const T a = static_cast<const T *>(D.oa)[j] + rc;

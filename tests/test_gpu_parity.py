@@ -293,6 +293,44 @@ def test_obstacles_parked_at_infinity(value, n, dtype):
         assert np.abs(out["lam"] - ost["lam"]).max() < 1e-5 * (1.0 + np.abs(ost["lam"]).max())
 
 
+@pytest.mark.parametrize("dtype,waves", [("f64", 2), ("f32", 2), ("f32", 3)])
+@pytest.mark.parametrize("n", [1, 3, 34])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_obstacles_that_come_and_go(value, n, dtype, waves):
+    """Obstacles without a place for part of the horizon, none of them there at
+    every time step of either wavefront, act where they are; reference as
+    above.  (Static ones around the path, so that trajectories meet them.)"""
+    import dataclasses
+    from paper_2109_13030_amd import am
+    cfg = dataclasses.replace(inputs.CONFIGS["c2"], n_obs=n, dynamic=False)
+    pb = inputs.make_problem(cfg, 83 + n)
+    pb["ox"][0], pb["oy"][0] = 4.6, 5.3   # beside the middle of the line from (1, 1) to (9, 9)
+    init = inputs.make_initial(pb, 5, 84, cfg.sigma)
+
+    def gone(v):
+        ox, oy = pb["ox"].copy(), pb["oy"].copy()
+        for j in range(n):
+            for at in ((20 + 7 * j) % 47, 50 + (21 + 11 * j) % 47):   # a few time steps in each half
+                ox[j, at:at + 3] = oy[j, at:at + 3] = v
+        for half in (slice(0, 50), slice(50, 100)):
+            assert np.isfinite(v) or not np.isfinite(ox[:, half]).all(1).any()
+        return dict(pb, ox=ox, oy=oy)
+    far = gone(1e4)
+    h = am.Handle.for_problem(gone(value), dtype)
+    h.waves = waves
+    _, _, st = H.run_gpu(gone(value), init, 10, dtype, handle=h)
+    out = st.numpy()
+    assert all(np.isfinite(out[k]).all() for k in st.KEYS)
+    orc, ost = H.run_oracle(far, init, 10)
+    free = H.run_oracle(dict(far, ox=far["ox"] + 1e4), init, 10)[1]
+    assert np.abs(ost["cx"] - free["cx"]).max() > 0.1   # the obstacles act
+    if dtype == "f32":
+        _fp32_gate(far, init, 10, out=out)
+        return
+    epos, epsi = H.traj_errors(far, out, orc, ost)
+    assert epos.max() < 1e-8 and epsi.max() < 1e-8
+
+
 @pytest.mark.parametrize("flags", [0, oracle.XTILDE_SLACK])
 @pytest.mark.parametrize("K", [0, 5])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
