@@ -121,10 +121,12 @@ typedef struct {
 } am_shape;
 
 /* One problem instance shared by the batch (Sec. II-B: all trajectories have
- * the same boundary conditions and obstacles).  An obstacle that is not needed
- * (n is fixed by the handle) may be placed at infinity for the whole horizon:
- * it then has no effect on the trajectories (default reading of alpha), its
- * alpha and d are of no use and AM_RES_FC_RMS is NaN. */
+ * the same boundary conditions and obstacles).  An obstacle that is not there
+ * (n is fixed by the handle) may be placed at infinity, for the whole horizon
+ * or a part of it: it then has no effect on the trajectories at those time
+ * steps (default reading of alpha; where a circle's centre falls exactly on
+ * another obstacle's, the result is NaN), its alpha and d there are of no use
+ * and AM_RES_FC_RMS is NaN. */
 typedef struct {
   const void *obs_x;    /* device [n][q] obstacle centre x_j(t_k)             */
   const void *obs_y;    /* device [n][q] obstacle centre y_j(t_k)             */
