@@ -193,7 +193,7 @@ __device__ __forceinline__ T row_dot(const T *op, int I, const T *v) {
 // (16 trajectories, 50 iterations) went from 611 to 204 us, FP64 with 5 (501
 // trajectories, 20 iterations, q = 127) from 558 to 133, FP32 with 8 (333
 // trajectories, 40 obstacles, 20 iterations) from 183 to 173; with the list
-// and set-up steps below and the FP64 square root they take 190, 99 and 141.
+// and set-up steps below and the FP64 square root they take 190, 94 and 128.
 template <typename T, int NV, int C, int RED>
 __device__ __forceinline__ void fused_body(const Desc &Dsrc, int l, bool live, int half, T *lds, const FusedLds &L,
                            int lane, int wave) {

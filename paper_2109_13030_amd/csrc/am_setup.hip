@@ -19,7 +19,7 @@
 // reduction per Gram-Schmidt coefficient) took 556 us; these take 59 + 13 us
 // (q = 100, nv = 11, set-ups repeated: basis 8, QR 17, elimination 25, Gram
 // matrices 2 us; as the only one of a process the second kernel, whose
-// unrolled jobs hold 368 bytes of scratch a lane, took 14 to 70 us).
+// unrolled jobs hold 368 bytes of scratch a lane, took 14 to 75 us).
 #include <hip/hip_runtime.h>
 
 #include "am_device.h"
